@@ -23,13 +23,13 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wno-unused-command-line-argument",
 ]
-# per-source flags: the d = 64 kernels (128- and 256-row tiles) run faster
+# per-source flags: the forward and the d = 64 kernels (128- and 256-row tiles) run faster
 # with their MFMA results in VGPRs (S and dP feed the softmax without AGPR
 # reads), and the d = 256 kernel compiles that way without the VGPR spills
 # (and scratch) it has otherwise; the d = 128 kernel, with less room in its
 # VGPRs, runs slower that way
 _VGPR_MFMA = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
-SOURCE_FLAGS = {"attn_bwd_d64.hip": _VGPR_MFMA, "attn_bwd64w.hip": _VGPR_MFMA, "attn_bwd256.hip": _VGPR_MFMA}
+SOURCE_FLAGS = {"attn_fwd.hip": _VGPR_MFMA, "attn_bwd_d64.hip": _VGPR_MFMA, "attn_bwd64w.hip": _VGPR_MFMA, "attn_bwd256.hip": _VGPR_MFMA}
 
 
 def hipcc() -> str:

@@ -39,6 +39,11 @@ template <>
 DASH_LDS_HD int tile_swz<64>(int r) {
   return ((r >> 1) & 1) | (((r >> 2) & 1) << 1) | ((((r >> 1) ^ (r >> 3)) & 1) << 2);
 }
+// D = 256 (512-byte rows, two bank cycles): as D = 128 on the low 4 chunk bits.
+template <>
+DASH_LDS_HD int tile_swz<256>(int r) {
+  return tile_swz<128>(r);
+}
 // element index of (row r, column col) in a [rows][D] bf16 tile
 template <int D>
 DASH_LDS_HD int bf_at(int r, int col) {
