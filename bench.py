@@ -126,7 +126,7 @@ def measured_traffic():
     FETCH_SIZE / WRITE_SIZE summary, or None if the kernel source changed since
     the counters were taken."""
     import hashlib
-    summary = os.path.join(ROOT, "profiles", "bwd_main_b2h16n8192d128_full.md")
+    summary = os.path.join(ROOT, "profiles", "bwd_mainw_b2h16n8192d128_full.md")
     try:
         text = open(summary).read()
         fields = dict(line.split(": ", 1) for line in text.splitlines() if ": " in line and not line.startswith(" "))
@@ -285,7 +285,9 @@ def main():
     placement = "global" if det == "atomic" else \
         ("XCD-local" if dash.dash_bwd_placement(B, H, N, d, causal, det) == dash.DASH_PLACEMENT_XCD else "global")
     bc = dash.dash_schedule_table(det, N, d, causal, heads=B * H)["bc"]
-    kname = "bwd_main256_kernel" if d == 256 else ("bwd_main64w_kernel" if bc == 256 else "bwd_main_kernel")
+    wide = bc == (128 if d == 256 else 256)
+    kname = {(64, True): "bwd_main64w_kernel", (128, True): "bwd_mainw_kernel", (256, True): "bwd_mainw_kernel",
+             (256, False): "bwd_main256_kernel"}.get((d, wide), "bwd_main_kernel")
     out = {
         "metric": "deterministic attn-bwd TFLOPS (bf16, d=128, N=8192) + % of atomic variant",
         "value": round(tflops, 2),

@@ -308,10 +308,12 @@ int dash_mfma_peak(int iters, double* tflops);
 /*
  * Host-side view of the schedule the kernels follow (no GPU needed).  For one
  * head of length N at head dim d, in a call of `heads` = B*H heads: T_r
- * scheduling Q tiles of br rows and T_c KV tiles of bc rows (bc = 128 at
- * d = 128 and 64 at d = 256; at d = 64, 256 when the call has at least 256 KV
- * tiles of 256 rows over all heads (causal: 512 and N >= 1024), else 128 --
- * so the summation order depends on the call's number of heads at d = 64),
+ * scheduling Q tiles of br rows and T_c KV tiles of bc rows.  bc is 128 at
+ * d = 64 and 128 and 64 at d = 256, and twice that when the call has tiles of
+ * that size enough over all heads: at least 256 at d = 64 (causal: 512 and
+ * N >= 1024), 160 at d = 128 (causal: 384 and N > 256), 128 at d = 256 (causal:
+ * 192; more than one head); at d = 128 and 256 not for ATOMIC and SPLIT -- so
+ * the summation order depends on the call's number of heads,
  * under `placement` (DASH_PLACEMENT_GLOBAL or DASH_PLACEMENT_XCD; only
  * Shift's groups depend on it).  Writes, when the pointer is non-NULL:
  *   geometry[6]            = {T_r, T_c, br, number of workgroup chains per

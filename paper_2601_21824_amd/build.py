@@ -12,7 +12,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libdash.so")
-SOURCES = ["attn_fwd.hip", "attn_bwd.hip", "attn_bwd_d64.hip", "attn_bwd64w.hip", "attn_bwd256.hip", "attn_dq.hip", "mfma_peak.hip",
+SOURCES = ["attn_fwd.hip", "attn_bwd.hip", "attn_bwd_d64.hip", "attn_bwd64w.hip", "attn_bwd256.hip", "attn_bwdw.hip", "attn_dq.hip", "mfma_peak.hip",
            "dash_api.hip"]
 HEADERS = ["common.h", "kernels.h", "schedule.h", "bwd_common.h", "bwd_main.h", "lds_layout.h", "dag_model.h", "model_calibration.h"]
 
@@ -29,7 +29,8 @@ HIPCC_FLAGS = [
 # (and scratch) it has otherwise; the d = 128 kernel, with less room in its
 # VGPRs, runs slower that way
 _VGPR_MFMA = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
-SOURCE_FLAGS = {"attn_fwd.hip": _VGPR_MFMA, "attn_bwd_d64.hip": _VGPR_MFMA, "attn_bwd64w.hip": _VGPR_MFMA, "attn_bwd256.hip": _VGPR_MFMA}
+SOURCE_FLAGS = {"attn_fwd.hip": _VGPR_MFMA, "attn_bwd_d64.hip": _VGPR_MFMA, "attn_bwd64w.hip": _VGPR_MFMA, "attn_bwd256.hip": _VGPR_MFMA,
+                "attn_bwdw.hip": _VGPR_MFMA}
 
 
 def hipcc() -> str:

@@ -166,11 +166,11 @@ hipError_t launch_all(const BwdArgs& a, long pre_blocks, int grid_main, hipStrea
   if (e != hipSuccess) return e;
   if (a.ev_begin) (void)hipEventRecord(a.ev_begin, stream);
   if constexpr (D == 256)
-    e = launch_main256(a, grid_main, stream);
+    e = a.G.bc == 128 ? launch_mainw(a, D, grid_main, stream) : launch_main256(a, grid_main, stream);
   else if constexpr (D == 64)
     e = a.G.bc == 256 ? launch_main64w(a, grid_main, stream) : launch_main64(a, grid_main, stream);
   else
-    e = launch_main<D>(a, grid_main, stream);
+    e = a.G.bc == 256 ? launch_mainw(a, D, grid_main, stream) : launch_main<D>(a, grid_main, stream);
   if (e != hipSuccess) return e;
   if (a.ev_end) (void)hipEventRecord(a.ev_end, stream);
   if (atomic) hipLaunchKernelGGL(bwd_post_kernel<D>, dim3(1024), dim3(256), 0, stream, a);
@@ -197,7 +197,8 @@ int bwd_main_occupancy(int d) {
     const int a = main64_occupancy(), b = bwd_main64w_occupancy();
     return a < b ? a : b;
   }
-  return d == 128 ? main_occupancy<128>() : bwd_main256_occupancy();
+  const int a = d == 128 ? main_occupancy<128>() : bwd_main256_occupancy(), b = bwd_mainw_occupancy(d);
+  return a < b ? a : b;
 }
 
 }  // namespace dash

@@ -173,6 +173,26 @@ __device__ inline void vm_wait_le(int n) {
   else vm_wait<0>();
 }
 
+// A wave's 32 x D block of dK or dV (the C layout of the 32x32 MFMA: acc[nb][r]
+// of lane l is row 8 (r/4) + 4 (l/32) + r%4, column 32 nb + l%32), times `scale`,
+// to rows row0 .. row0 + 31 of a [N][D] bf16 matrix, through `pad` (wave-private
+// LDS, 64 D bytes): one contiguous run of 16-byte stores instead of a 2-byte
+// store per element.
+template <int D>
+__device__ inline void store_block32(__amdgpu_buffer_rsrc_t r, void* pad, const f32x16 (&acc)[D / 32], float scale, int row0,
+                                     int l) {
+  unsigned short* p = (unsigned short*)pad + 4 * (l >> 5) * D + (l & 31);
+  asm volatile("" ::: "memory");  // after the pad's previous reads
+#pragma unroll
+  for (int nb = 0; nb < D / 32; ++nb)
+#pragma unroll
+    for (int k = 0; k < 16; ++k) p[(8 * (k >> 2) + (k & 3)) * D + 32 * nb] = to_bf16(acc[nb][k] * scale);
+  asm volatile("" ::: "memory");  // lanes read what other lanes wrote
+#pragma unroll
+  for (int i = 0; i < D / 16; ++i)
+    st16(r, (uint32_t)(row0 * D * 2 + 1024 * i + 16 * l), *(const u32x4*)((const char*)pad + 1024 * i + 16 * l));
+}
+
 // Launch a main-kernel instantiation on the persistent grid.  Shift and
 // Symmetric Shift chains wait on each other in a cycle, so every workgroup of
 // their grid must be resident at once: they launch cooperatively, and a grid

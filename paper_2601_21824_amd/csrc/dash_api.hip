@@ -45,8 +45,11 @@ Layout layout(int B, int H, int N, int d, int sched) {
   Layout L;
   const size_t bh = (size_t)B * H;
   const size_t nblk = ((size_t)N + dash::kBlockRows - 1) / dash::kBlockRows;
-  const int bc_f = dash::kv_tile_rows(d, 0, N, (long)bh), bc_c = dash::kv_tile_rows(d, 1, N, (long)bh);
-  const size_t bc = (size_t)(bc_f < bc_c ? bc_f : bc_c);  // PARTIALS: the more tiles of either mask
+  // PARTIALS: a copy per tile, room for the more tiles of either mask and (at
+  // d = 128) for narrow ones also where it takes wide ones, so that the size a
+  // caller has always got stays enough
+  const int bc_f = dash::kv_tile_rows(dash::S_SPLIT, d, 0, N, (long)bh), bc_c = dash::kv_tile_rows(dash::S_SPLIT, d, 1, N, (long)bh);
+  const size_t bc = (size_t)(bc_f < bc_c ? bc_f : bc_c);
   const size_t copies = sched == DASH_SCHED_PARTIALS ? ((size_t)N + bc - 1) / bc : 1;
   size_t off = 0;
   L.ctrl = off;
@@ -62,12 +65,18 @@ Layout layout(int B, int H, int N, int d, int sched) {
   // per-chain step tables: at most T_c + 1 chains (Symmetric Shift pads T_c
   // to even), each its length and at most (T_r + 1) * nsub steps (full mask:
   // 64-row Q tiles; causal: Symmetric Shift's padded T_r + 1 tasks); then the
-  // ticket order
-  const dash::Geom G = dash::make_geom(dash::S_SHIFT, 0, N, d, (long)bh);
-  const dash::Geom Gc = dash::make_geom(dash::S_SYMSHIFT, 1, N, d, (long)bh);
-  const int cap_f = (G.t_r + 1) * G.nsub, cap_c = (Gc.t_r + 1) * Gc.nsub;
-  L.step_cap = 1 + (cap_f > cap_c ? cap_f : cap_c);
-  const size_t chains = (size_t)(G.t_c > Gc.t_c ? G.t_c : Gc.t_c) + 1;
+  // ticket order.  The tile size, and with it both counts, depends on the
+  // schedule (kv_tile_rows): SPLIT's tiles are the smallest (most chains), the
+  // larger tiles of the others round T_r up further.
+  size_t chains = 0;
+  L.step_cap = 0;
+  for (int s : {(int)dash::S_SHIFT, (int)dash::S_SPLIT})
+    for (int c = 0; c < 2; ++c) {
+      const dash::Geom G = dash::make_geom(s == dash::S_SHIFT && c ? dash::S_SYMSHIFT : s, c, N, d, (long)bh);
+      const int cap = 1 + (G.t_r + 1) * G.nsub;
+      if (cap > L.step_cap) L.step_cap = cap;
+      if ((size_t)G.t_c + 1 > chains) chains = (size_t)G.t_c + 1;
+    }
   L.steps = off;
   off += align256(chains * L.step_cap * sizeof(unsigned));
   L.order = off;
@@ -322,10 +331,20 @@ double model_makespan(int sched, int B, int H, int N, int d, int causal, long wo
   const double m2 = dash::simulate_dag(G, hd, (int)(2 * head_cap), (int)workers, c, r);
   if (m1 < 0 || m2 < 0) return -1.0;
   const double line = m2 + (m2 - m1) * (double)(heads - 2 * head_cap) / (double)head_cap;
-  int longest = 0;
-  for (int w = 0; w < G.chains; ++w) longest = std::max(longest, hd.off[w + 1] - hd.off[w]);
-  const double bound = std::max((double)hd.off[G.chains] * (double)heads * (c + r) / (double)workers,
-                                (double)longest * (c + r));
+  int longest = 0, shortest = 1 << 30;
+  for (int w = 0; w < G.chains; ++w) {
+    longest = std::max(longest, hd.off[w + 1] - hd.off[w]);
+    shortest = std::min(shortest, hd.off[w + 1] - hd.off[w]);
+  }
+  double bound = std::max((double)hd.off[G.chains] * (double)heads * (c + r) / (double)workers,
+                          (double)longest * (c + r));
+  // chains of one length run in whole rounds, the last one partly idle (12
+  // chains per head, 200 heads, 256 workgroups: 10 rounds, which the line
+  // through 64 and 128 heads, 3 and 6 whole rounds, puts at 9.4)
+  if (shortest == longest) {
+    const double rounds = std::ceil((double)heads * (double)G.chains / (double)workers);
+    bound = std::max(bound, rounds * (double)longest * (c + r));
+  }
   return std::max(line, bound);
 }
 

@@ -79,6 +79,9 @@ int bwd_main64w_occupancy();
 // head dim 256 (attn_bwd256.hip)
 hipError_t launch_main256(const BwdArgs& a, int grid_main, hipStream_t stream);
 int bwd_main256_occupancy();
+// wide KV tiles at head dims 128 (256 rows) and 256 (128 rows) (attn_bwdw.hip)
+hipError_t launch_mainw(const BwdArgs& a, int d, int grid_main, hipStream_t stream);
+int bwd_mainw_occupancy(int d);
 // measured MFMA throughput (mfma_peak.hip): grid workgroups of 4 waves
 void launch_mfma_peak(int grid, int iters, float* sink, hipStream_t stream);
 double mfma_peak_flops_per_launch(int grid, int iters);

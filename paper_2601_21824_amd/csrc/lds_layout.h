@@ -63,6 +63,14 @@ DASH_LDS_HD int dst_at(int r, int q) {
   return r * 64 + (((q >> 2) ^ dst_swz(r)) << 2);
 }
 
+// ---- wide-tile kernels: dS^T tile [kv][32 q] bf16 (64-byte rows, four per bank
+// cycle).  8-byte slot s (4 queries) of row r is stored at slot s ^ (r / 4) % 8.
+// Writes: 32 consecutive rows at one slot per lane group; transposed reads: rows
+// r0 .. r0+3 (r0 a multiple of 4) x all 8 slots per lane group.
+DASH_LDS_HD int dst32_at(int r, int q) {
+  return r * 32 + (((q >> 2) ^ ((r >> 2) & 7)) << 2);
+}
+
 // ---- d = 256 kernel: [64][256] bf16 Q / dO tiles (512-byte rows)
 // Row operands: lane l reads row 16h + l%16 at chunk 4k + l/16; transposed
 // operands: lanes 0-31 read rows r0 .. r0+7 (r0 a multiple of 8), two chunks

@@ -46,7 +46,7 @@ namespace dash {
 enum Sched { S_ATOMIC = 0, S_NAIVE = 1, S_DESCENDING = 2, S_SHIFT = 3, S_SYMSHIFT = 4, S_PARTIALS = 6, S_SPLIT = 7 };
 
 constexpr int kBlockRows = 64;  // rows of a physical Q block (one counter each)
-constexpr int kTileKV = 128;    // KV rows per tile of the d = 128 kernel
+constexpr int kTileKV = 128;    // KV rows per tile of bwd_main_kernel (d = 64 and 128, narrow)
 constexpr int kMaxGroup = 256;  // Shift: KV-tile chains that must be co-resident
 constexpr int kXcdGroup = 32;   // ... under XCD-local placement (one XCD's resident workgroups)
 
@@ -64,26 +64,40 @@ struct Geom {
   int chain_major;  // work tickets chain-major (see ticket_chain), else head-major
 };
 
-// rows per KV tile: 128 at d = 128, 64 at d = 256.  At d = 64, 256 (the
-// 256-row kernel, half the accumulator traffic per FLOP) when the call has
-// KV tiles enough to keep a 256-CU GPU busy -- at least 256 of them over all
-// `heads` heads for a full mask, 512 and N >= 1024 for a causal one (whose
-// chains are uneven) -- else 128.  The tile size is part of the summation
-// order, so it is a function of the problem (d, mask, N, heads) alone, never
-// of the device.
-DASH_HD int kv_tile_rows(int d, int causal, int N, long heads) {
-  if (d == 64) {
-    const long wide = heads * (long)((N + 255) / 256);
-    return (causal ? (N >= 1024 && wide >= 512) : wide >= 256) ? 256 : 128;
-  }
-  return d == 128 ? 128 : 64;
+// rows per KV tile.  Every head dim has a narrow and a wide tile: 128 and 256
+// rows at d = 64 and 128, 64 and 128 at d = 256.  The wide one halves the
+// accumulator traffic per FLOP and is 1.1-1.9 times faster per FLOP, but a call
+// needs tiles enough to fill a 256-CU GPU, whose workgroups run one tile each:
+//  d = 64   256 wide tiles over all heads; causal (uneven chains) 512 and
+//           N >= 1024.
+//  d = 128  160 (narrow / wide time: 128 tiles 0.75-0.84, 192 tiles 1.23, 256
+//           tiles 1.16-1.30, 512 and more 1.14-1.28); causal 384 and N > 256
+//           (256 tiles 0.84-0.98, 384 tiles 1.23, 512 and more 1.06-1.28; N = 256
+//           0.99 at 512 tiles).
+//  d = 256  128 (64 tiles 0.97-1.11, 128 tiles 1.03-1.25, 256 and more 1.40-1.99);
+//           causal 192 (128 tiles 0.87-1.07, 192 tiles 1.18, 256 and more
+//           1.20-1.88); a call of one head keeps the narrow tile, whose Shift
+//           groups at N = 32768 are its documented geometry.
+// The atomic variant and SPLIT's dK, dV pass (no ordered accumulator) exist for
+// the narrow tile only at d = 128 and 256.  The tile size is part of the
+// summation order, so it is a function of the problem (schedule, d, mask, N,
+// heads) alone, never of the device.
+DASH_HD int kv_tile_rows(int sched, int d, int causal, int N, long heads) {
+  const int narrow = d == 256 ? 64 : 128;
+  const long wide = heads * (long)((N + 2 * narrow - 1) / (2 * narrow));
+  bool w;
+  if (d == 64) w = causal ? (N >= 1024 && wide >= 512) : wide >= 256;
+  else if (sched == S_ATOMIC || sched == S_SPLIT) w = false;
+  else if (d == 128) w = causal ? (N > 256 && wide >= 384) : wide >= 160;
+  else w = heads > 1 && wide >= (causal ? 192 : 128);
+  return w ? 2 * narrow : narrow;
 }
 
 DASH_HD Geom make_geom(int sched, int causal, int N, int d, long heads) {
   Geom G;
   G.sched = sched;
   G.causal = causal ? 1 : 0;
-  G.bc = kv_tile_rows(d, causal, N, heads);
+  G.bc = kv_tile_rows(sched, d, causal, N, heads);
   G.br = causal ? G.bc : kBlockRows;
   G.g = G.bc / G.br;
   G.t_c = (N + G.bc - 1) / G.bc;
