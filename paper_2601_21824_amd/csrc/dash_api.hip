@@ -33,8 +33,11 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
   size_t ctrl, dqacc, dvec, lse2, counters, steps, order, total;
-  int step_cap;
 };
+
+// entries of a chain's step table: its length and at most (T_r + 1) * nsub steps
+// (full mask: 64-row Q tiles; causal: Symmetric Shift's padded T_r + 1 tasks)
+int step_cap(const dash::Geom& G) { return 1 + (G.t_r + 1) * G.nsub; }
 
 // ctrl first so that dash_bwd_check can find it without the problem size.
 // The layout depends on the schedule only through PARTIALS, which keeps one
@@ -62,23 +65,22 @@ Layout layout(int B, int H, int N, int d, int sched) {
   off += align256(bh * N * sizeof(float));
   L.counters = off;
   off += align256(bh * nblk * dash::kCtrStride * sizeof(int));
-  // per-chain step tables: at most T_c + 1 chains (Symmetric Shift pads T_c
-  // to even), each its length and at most (T_r + 1) * nsub steps (full mask:
-  // 64-row Q tiles; causal: Symmetric Shift's padded T_r + 1 tasks); then the
-  // ticket order.  The tile size, and with it both counts, depends on the
-  // schedule (kv_tile_rows): SPLIT's tiles are the smallest (most chains), the
-  // larger tiles of the others round T_r up further.
-  size_t chains = 0;
-  L.step_cap = 0;
+  // per-chain step tables (step_cap entries each), at most T_c + 1 chains
+  // (Symmetric Shift pads T_c to even), then the ticket order.  The tile size,
+  // and with it both counts, depends on the schedule (kv_tile_rows): the tables
+  // of narrow and of wide tiles each need their own product, which for wide
+  // tiles (half the chains) is the smaller one, so that the size is the narrow
+  // tiles' wherever a call may take either.
+  size_t chains = 0, entries = 0;
   for (int s : {(int)dash::S_SHIFT, (int)dash::S_SPLIT})
     for (int c = 0; c < 2; ++c) {
       const dash::Geom G = dash::make_geom(s == dash::S_SHIFT && c ? dash::S_SYMSHIFT : s, c, N, d, (long)bh);
-      const int cap = 1 + (G.t_r + 1) * G.nsub;
-      if (cap > L.step_cap) L.step_cap = cap;
-      if ((size_t)G.t_c + 1 > chains) chains = (size_t)G.t_c + 1;
+      const size_t n = (size_t)G.t_c + 1;
+      if (n * step_cap(G) > entries) entries = n * step_cap(G);
+      if (n > chains) chains = n;
     }
   L.steps = off;
-  off += align256(chains * L.step_cap * sizeof(unsigned));
+  off += align256(entries * sizeof(unsigned));
   L.order = off;
   off += align256((bh + dash::kMaxXcd) * chains * 2 * sizeof(int));  // XCD segments round up per XCD
   L.total = off;
@@ -546,7 +548,7 @@ int bwd_launch(const void* q, const void* k, const void* v, const void* o, const
   a.counters = (int*)(ws + L.counters);
   a.ctrl = (int*)(ws + L.ctrl);
   a.steps = (unsigned*)(ws + L.steps);
-  a.step_cap = L.step_cap;
+  a.step_cap = step_cap(G);
   a.order = (int*)(ws + L.order);
   a.nxcd = xcd ? di.nxcd : 0;
   a.xcd_cap = xcd_cap;
