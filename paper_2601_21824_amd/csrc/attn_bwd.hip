@@ -21,39 +21,57 @@ namespace dash {
 
 
 // ---------------------------------------------------------------- bwd_pre
-template <int D>
+// Memory-bound: O and dO are read once.  A wave takes U times 64 / TPR rows in
+// a row, all their loads issued before the first is used, and writes their D
+// and L with one store each.  O, which nothing reads again, is loaded past the
+// caches that dO stays in for the main kernel.
+// Measured (us, one row per thread -> four): 16 MB of O and dO each 8.1 -> 7.1,
+// 67 MB 27.4 -> 22.9 (5.9 TB/s), 134 MB 55.4 -> 53.3.
+template <int D, int U>
 __global__ __launch_bounds__(256) void bwd_pre_kernel(BwdArgs a, int zero_acc) {
-  constexpr int TPR = D / 8;  // threads per row, 8 elements each
-  const long gtid = (long)blockIdx.x * 256 + threadIdx.x;
+  constexpr int TPR = D / 8;    // threads per row, 8 elements each
+  constexpr int RPL = 64 / TPR;  // rows of a wave's load instruction
+  static_assert(U <= TPR, "lane c of a row writes row c of its U");
+  const unsigned gtid = blockIdx.x * 256u + threadIdx.x;  // (at most 2^24 threads)
+  const unsigned nthreads = gridDim.x * 256u;
   const long rows = (long)a.bh * a.n;
-  const long row = gtid / TPR;
-  const int c = (int)(gtid % TPR);
-  float acc = 0.f;
-  if (row < rows) {
-    const __bf16* pdo = (const __bf16*)a.dO + row * D + 8 * c;
-    const __bf16* po = (const __bf16*)a.o + row * D + 8 * c;
-    const u32x4 x = *(const u32x4*)pdo;
-    const u32x4 y = *(const u32x4*)po;
+  const int l = threadIdx.x & 63, c = l % TPR;
+  // the grid covers every row once, except where the number of workgroups is capped
+  for (long row0 = (long)(gtid >> 6) * (RPL * U); row0 < rows; row0 += (long)(nthreads >> 6) * (RPL * U)) {
+    u32x4 x[U], y[U];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float xf = bf16_to_f32((unsigned short)(x[e >> 1] >> (16 * (e & 1))));
-      const float yf = bf16_to_f32((unsigned short)(y[e >> 1] >> (16 * (e & 1))));
-      acc = __builtin_fmaf(xf, yf, acc);
+    for (int u = 0; u < U; ++u) {
+      long row = row0 + u * RPL + l / TPR;
+      row = row < rows ? row : rows - 1;  // (read, not written)
+      x[u] = *(const u32x4*)((const __bf16*)a.dO + row * D + 8 * c);
+      y[u] = __builtin_nontemporal_load((const u32x4*)((const __bf16*)a.o + row * D + 8 * c));
+    }
+    float mine = 0.f;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float acc = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float xf = bf16_to_f32((unsigned short)(x[u][e >> 1] >> (16 * (e & 1))));
+        const float yf = bf16_to_f32((unsigned short)(y[u][e >> 1] >> (16 * (e & 1))));
+        acc = __builtin_fmaf(xf, yf, acc);
+      }
+      // butterfly over the TPR lanes of a row: a+b == b+a exactly, so every lane
+      // ends with the same bits and the tree is fixed
+#pragma unroll
+      for (int off = 1; off < TPR; off <<= 1) acc += __shfl_xor(acc, off);
+      mine = c == u ? acc : mine;
+    }
+    const long row = row0 + c * RPL + l / TPR;
+    if (c < U && row < rows) {
+      a.dvec[row] = mine;
+      a.lse2[row] = a.lse[row] * kLog2e;
     }
   }
-  // butterfly over the TPR lanes of a row: a+b == b+a exactly, so every lane
-  // ends with the same bits and the tree is fixed
-#pragma unroll
-  for (int off = 1; off < TPR; off <<= 1) acc += __shfl_xor(acc, off);
-  if (row < rows && c == 0) {
-    a.dvec[row] = acc;
-    a.lse2[row] = a.lse[row] * kLog2e;
-  }
 
-  const long nthreads = (long)gridDim.x * 256;
-  const long nctr = (long)a.bh * a.nblk;
+  const unsigned nctr = (unsigned)a.bh * (unsigned)a.nblk;
   const int init = a.poison ? kPoison : 0;
-  for (long i = gtid; i < nctr; i += nthreads) a.counters[i * kCtrStride] = init;
+  for (unsigned i = gtid; i < nctr; i += nthreads) a.counters[(size_t)i * kCtrStride] = init;
   if (gtid == 0) {
     a.ctrl[kCtrlTicket] = 0;
     a.ctrl[kCtrlError] = 0;
@@ -67,9 +85,9 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(BwdArgs a, int zero_acc) {
   {
     const Geom& G = a.G;
     const int bc = G.bc;
-    const long ntab = (long)G.chains * a.step_cap;
-    for (long x = gtid; x < ntab; x += nthreads) {
-      const int w = (int)(x / a.step_cap), e = (int)(x % a.step_cap);
+    const unsigned ntab = (unsigned)G.chains * (unsigned)a.step_cap;
+    for (unsigned x = gtid; x < ntab; x += nthreads) {
+      const int w = (int)(x / (unsigned)a.step_cap), e = (int)(x % (unsigned)a.step_cap);
       const int len = chain_len(G, w) * G.nsub;
       if (e == 0) {
         a.steps[x] = (unsigned)len;
@@ -86,28 +104,28 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(BwdArgs a, int zero_acc) {
     // work ticket -> (head, chain); XCD-local placement: one segment of
     // xcd_cap tickets per XCD
     if (a.nxcd > 0) {
-      const long nitems = (long)a.nxcd * a.xcd_cap;
-      for (long x = gtid; x < nitems; x += nthreads) {
-        const int q = (int)(x / a.xcd_cap), t = (int)(x % a.xcd_cap);
+      const unsigned nitems = (unsigned)a.nxcd * (unsigned)a.xcd_cap;
+      for (unsigned x = gtid; x < nitems; x += nthreads) {
+        const int q = (int)(x / (unsigned)a.xcd_cap), t = (int)(x % (unsigned)a.xcd_cap);
         if (t >= xcd_heads(a.bh, a.nxcd, q) * G.chains) continue;
         int bh, w;
         ticket_chain_xcd(G, a.bh, a.nxcd, q, t, &bh, &w);
-        a.order[2 * x] = bh;
-        a.order[2 * x + 1] = w;
+        a.order[2 * (size_t)x] = bh;
+        a.order[2 * (size_t)x + 1] = w;
       }
     } else {
-      const long nitems = (long)a.bh * G.chains;
-      for (long x = gtid; x < nitems; x += nthreads) {
+      const unsigned nitems = (unsigned)a.bh * (unsigned)G.chains;
+      for (unsigned x = gtid; x < nitems; x += nthreads) {
         int bh, w;
         ticket_chain(G, a.bh, (int)x, &bh, &w);
-        a.order[2 * x] = bh;
-        a.order[2 * x + 1] = w;
+        a.order[2 * (size_t)x] = bh;
+        a.order[2 * (size_t)x + 1] = w;
       }
     }
   }
   if (zero_acc) {
     const long n4 = (long)a.bh * a.n * D / 4;
-    for (long i = gtid; i < n4; i += nthreads) ((f32x4*)a.dqacc)[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (long i = gtid; i < n4; i += (long)nthreads) ((f32x4*)a.dqacc)[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 }
 
@@ -159,9 +177,18 @@ __global__ __launch_bounds__(256) void bwd_sum_partials_kernel(BwdArgs a) {
 }
 
 template <int D>
-hipError_t launch_all(const BwdArgs& a, long pre_blocks, int grid_main, hipStream_t stream) {
+hipError_t launch_all(const BwdArgs& a, int grid_main, hipStream_t stream) {
   const bool atomic = a.G.sched == S_ATOMIC;
-  hipLaunchKernelGGL(bwd_pre_kernel<D>, dim3((unsigned)pre_blocks), dim3(256), 0, stream, a, (int)atomic);
+  // four rows per thread from 4096 such workgroups on (d = 64 / 128 / 256: 8.0
+  // -> 7.2 us there, 27 -> 23 at 16384); at 2048 both take 5.0 and below that
+  // (1024: 4.2-4.6 against 4.3-4.8) more waves are worth more
+  const long one = ((long)a.bh * a.n * (D / 8) + 255) / 256;  // workgroups of one row per thread group
+  if (one >= 4096) {
+    const long blocks = (one + 3) / 4;
+    hipLaunchKernelGGL((bwd_pre_kernel<D, 4>), dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0, stream, a, (int)atomic);
+  } else {
+    hipLaunchKernelGGL((bwd_pre_kernel<D, 1>), dim3((unsigned)one), dim3(256), 0, stream, a, (int)atomic);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (a.ev_begin) (void)hipEventRecord(a.ev_begin, stream);
@@ -182,14 +209,9 @@ hipError_t launch_all(const BwdArgs& a, long pre_blocks, int grid_main, hipStrea
 }
 
 hipError_t launch_bwd(const BwdArgs& a, int d, int grid_main, hipStream_t stream) {
-  const long rows = (long)a.bh * a.n;
-  const int tpr = d / 8;
-  long pre_blocks = (rows * tpr + 255) / 256;
-  if (pre_blocks < 1) pre_blocks = 1;
-  if (pre_blocks > 65535L * 16) pre_blocks = 65535L * 16;
-  if (d == 64) return launch_all<64>(a, pre_blocks, grid_main, stream);
-  if (d == 128) return launch_all<128>(a, pre_blocks, grid_main, stream);
-  return launch_all<256>(a, pre_blocks, grid_main, stream);
+  if (d == 64) return launch_all<64>(a, grid_main, stream);
+  if (d == 128) return launch_all<128>(a, grid_main, stream);
+  return launch_all<256>(a, grid_main, stream);
 }
 
 int bwd_main_occupancy(int d) {
