@@ -253,20 +253,24 @@ __global__ __launch_bounds__(256) void bwd_main64w_kernel(BwdArgs a) {
       // half 1 with its dS^T stores -- so only one key block's S and dP
       // (64 registers) are live at a time.
       //
+      // LDS operands of a run's four slots.  Slot k's MFMAs are followed by the
+      // reads of the next run's slot k into the registers they free, so a run
+      // starts without waiting for LDS (each of the nine runs of a step did):
+      // 64 heads of 8192 full 3971 -> 3920 us, causal 2244 -> 2192; forward and
+      // backward of 128 heads of 2100 causal 478.7 -> 469.9.  Keeping dK and dV in
+      // AGPRs by asm besides, as bwd_mainw_kernel does, takes the register moves
+      // out of the step but measured 1-3% slower.
+      bf16x8 fq[4], fo[4];
+      static_assert(KS == 4 && 2 * NB == 4, "four slots per run");
       // S = Q K^T, dP = dO V^T of query half qb and key block kb: A = Q / dO
-      // rows from LDS (all four k-steps read up front), B = K / V rows from
-      // registers
+      // rows from LDS, B = K / V rows from registers
+      auto rd_rows = [&](int qb, int ks) {  // row 32qb + lc: rows 32 apart share the swizzle
+        const uint32_t off = (uint32_t)bf_at<D>(slf & 31, 16 * ks + 8 * (slf >> 5)) * 2 + 32 * qb * D * 2;
+        fq[ks] = at16(qs, off);
+        fo[ks] = at16(dos, off);
+      };
       f32x16 s[2], dp[2];
-      auto sdp = [&](int qb, int kb, auto&& extra) {
-        bf16x8 rq[KS], ro[KS];
-        const int lf = slf;
-        // row 32qb + lc: rows 32 apart share the swizzle
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          const uint32_t off = (uint32_t)bf_at<D>(lf & 31, 16 * ks + 8 * (lf >> 5)) * 2 + 32 * qb * D * 2;
-          rq[ks] = at16(qs, off);
-          ro[ks] = at16(dos, off);
-        }
+      auto sdp = [&](int qb, int kb, auto&& next, auto&& extra) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           s[qb][r] = 0.f;
@@ -275,8 +279,9 @@ __global__ __launch_bounds__(256) void bwd_main64w_kernel(BwdArgs a) {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
           __builtin_amdgcn_sched_barrier(0);
-          s[qb] = mfma32(rq[ks], kreg[kb][ks], s[qb]);
-          dp[qb] = mfma32(ro[ks], vreg[kb][ks], dp[qb]);
+          s[qb] = mfma32(fq[ks], kreg[kb][ks], s[qb]);
+          dp[qb] = mfma32(fo[ks], vreg[kb][ks], dp[qb]);
+          next(ks);
           extra(ks);
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -334,39 +339,53 @@ __global__ __launch_bounds__(256) void bwd_main64w_kernel(BwdArgs a) {
       // dV += P^T dO and dK += dS^T Q of key block kb, query half qb:
       // A = P^T, dS^T from registers, B = dO^T, Q^T by transposed reads;
       // iteration k = (d block, 16-query half)
-      auto dvdk = [&](int qb, int kb, auto&& extra) {
-        constexpr int NP = 2 * NB;
-        const int lf = slf;
+      auto rd_cols = [&](int qb, int k) {
         // rows 32qb + 16half + x and x + 8 (x < 8): the swizzle of x and x + 8
-        auto rd = [&](int k, bf16x8* bo, bf16x8* bq) {
-          const int nb = k >> 1, half = k & 1;
-          const int col = 32 * nb + 16 * ((lf >> 4) & 1) + 4 * (lf & 3);
-          const int x = 4 * (lf >> 5) + ((lf & 15) >> 2);
-          const uint32_t m = (uint32_t)(32 * qb + 16 * half) * D * 2;
-          const uint32_t o0 = (uint32_t)bf_at<D>(x, col) * 2 + m, o1 = (uint32_t)bf_at<D>(x + 8, col) * 2 + m;
-          *bo = as_bf16x8(tr_at(dos, o0), tr_at(dos, o1));
-          *bq = as_bf16x8(tr_at(qs, o0), tr_at(qs, o1));
-        };
-        bf16x8 ro[NP], rq[NP];
-#pragma unroll
-        for (int k = 0; k < NP; ++k) rd(k, &ro[k], &rq[k]);
+        const int nb = k >> 1, half = k & 1, lf = slf;
+        const int col = 32 * nb + 16 * ((lf >> 4) & 1) + 4 * (lf & 3);
+        const int x = 4 * (lf >> 5) + ((lf & 15) >> 2);
+        const uint32_t m = (uint32_t)(32 * qb + 16 * half) * D * 2;
+        const uint32_t o0 = (uint32_t)bf_at<D>(x, col) * 2 + m, o1 = (uint32_t)bf_at<D>(x + 8, col) * 2 + m;
+        fo[k] = as_bf16x8(tr_at(dos, o0), tr_at(dos, o1));
+        fq[k] = as_bf16x8(tr_at(qs, o0), tr_at(qs, o1));
+      };
+      auto dvdk = [&](int qb, int kb, auto&& next, auto&& extra) {
+        constexpr int NP = 2 * NB;
 #pragma unroll
         for (int k = 0; k < NP; ++k) {
           __builtin_amdgcn_sched_barrier(0);
           const int nb = k >> 1, half = k & 1;
-          dvacc[kb][nb] = mfma32(pbf[qb][half], ro[k], dvacc[kb][nb]);
-          dkacc[kb][nb] = mfma32(dsbf[qb][half], rq[k], dkacc[kb][nb]);
+          dvacc[kb][nb] = mfma32(pbf[qb][half], fo[k], dvacc[kb][nb]);
+          dkacc[kb][nb] = mfma32(dsbf[qb][half], fq[k], dkacc[kb][nb]);
+          next(k);
           extra(k);
         }
         __builtin_amdgcn_sched_barrier(0);
       };
 
+      // dQ^T's operands, k-step ks (keys 16ks + x and x + 4, x < 12): the K
+      // tile's swizzle repeats every 16 rows, dS^T's every 32 (two bases, even
+      // and odd ks)
+      auto rd_kt = [&](int ks) {
+        const int x = 8 * (slf >> 5) + ((slf & 15) >> 2), dc = 32 * dblk + 16 * ((slf >> 4) & 1) + 4 * (slf & 3);
+        const uint32_t mk = (uint32_t)(16 * ks) * D * 2;
+        return as_bf16x8(tr_at(sm.kt, (uint32_t)bf_at<D>(x, dc) * 2 + mk), tr_at(sm.kt, (uint32_t)bf_at<D>(x + 4, dc) * 2 + mk));
+      };
+      auto rd_ds = [&](int ks) {
+        const int x = 8 * (slf >> 5) + ((slf & 15) >> 2), p = ks & 1, qc = 32 * qh0 + 16 * ((slf >> 4) & 1) + 4 * (slf & 3);
+        const uint32_t md = (uint32_t)(16 * (ks - p)) * BM * 2;
+        return as_bf16x8(tr_at(sm.dst, (uint32_t)dst_at(x + 16 * p, qc) * 2 + md),
+                         tr_at(sm.dst, (uint32_t)dst_at(x + 4 + 16 * p, qc) * 2 + md));
+      };
+
       bool early_acc = false;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) rd_rows(0, ks);
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb) {
         // run 1: S/dP of half 0 (key block 0: with the next block's Q / dO /
         // L / D prefetch)
-        sdp(0, kb, [&](int ks) {
+        sdp(0, kb, [&](int k) { rd_rows(1, k); }, [&](int ks) {
           if (kb > 0 || pb_next < 0) return;
           if (ks < QLD) load_part(pb_next, buf ^ 1, ks);
           if (ks == 0) load_ld(pb_next, buf ^ 1);
@@ -393,7 +412,7 @@ __global__ __launch_bounds__(256) void bwd_main64w_kernel(BwdArgs a) {
         read_ld(0, 0);
         // run 2: S/dP of half 1, with softmax of half 0 (key block 0: and the
         // accumulator fetch)
-        sdp(1, kb, [&](int ks) {
+        sdp(1, kb, [&](int k) { rd_cols(0, k); }, [&](int ks) {
 #pragma unroll
           for (int p = 2 * ks; p < 2 * ks + 2; ++p) softmax_piece(0, kb, p);
           if (kb == 0 && early_acc && ks == 0) load_acc(pb);
@@ -408,12 +427,15 @@ __global__ __launch_bounds__(256) void bwd_main64w_kernel(BwdArgs a) {
           }
         }
         // run 3: dV/dK of half 0, with softmax of half 1
-        dvdk(0, kb, [&](int k) {
+        dvdk(0, kb, [&](int k) { rd_cols(1, k); }, [&](int k) {
 #pragma unroll
           for (int p = 2 * k; p < 2 * k + 2; ++p) softmax_piece(1, kb, p);
         });
         // run 4: dV/dK of half 1, with the dS^T stores
         dvdk(1, kb, [&](int k) {
+          if (kb + 1 < KB) rd_rows(0, k);
+          else if constexpr (MODE != kModeNoDq) fq[k] = rd_kt(k);  // (dQ^T's K side: the tile stands)
+        }, [&](int k) {
           if constexpr (MODE != kModeNoDq) {
 #pragma unroll
             for (int p = 2 * k; p < 2 * k + 2; ++p) store_ds_piece(kb, p);
@@ -434,27 +456,16 @@ __global__ __launch_bounds__(256) void bwd_main64w_kernel(BwdArgs a) {
         for (int r = 0; r < 16; ++r) dq[r] = 0.f;
         {
           constexpr int RING = 4;
-          const int lf = slf;
-          // keys 16ks + x and x + 4 (x < 12): the K tile's swizzle repeats
-          // every 16 rows, dS^T's every 32 (two bases, even and odd ks)
-          auto rd = [&](int ks, bf16x8* ka, bf16x8* db) {
-            const int x = 8 * (lf >> 5) + ((lf & 15) >> 2), p = ks & 1;
-            const int dc = 32 * dblk + 16 * ((lf >> 4) & 1) + 4 * (lf & 3);
-            const int qc = 32 * qh0 + 16 * ((lf >> 4) & 1) + 4 * (lf & 3);
-            const uint32_t mk = (uint32_t)(16 * ks) * D * 2, md = (uint32_t)(16 * (ks - p)) * BM * 2;
-            *ka = as_bf16x8(tr_at(sm.kt, (uint32_t)bf_at<D>(x, dc) * 2 + mk),
-                            tr_at(sm.kt, (uint32_t)bf_at<D>(x + 4, dc) * 2 + mk));
-            *db = as_bf16x8(tr_at(sm.dst, (uint32_t)dst_at(x + 16 * p, qc) * 2 + md),
-                            tr_at(sm.dst, (uint32_t)dst_at(x + 4 + 16 * p, qc) * 2 + md));
-          };
-          bf16x8 ka[RING], db[RING];
 #pragma unroll
-          for (int k = 0; k < RING; ++k) rd(k, &ka[k], &db[k]);
+          for (int k = 0; k < RING; ++k) fo[k] = rd_ds(k);
 #pragma unroll
           for (int ks = 0; ks < KSC; ++ks) {
             __builtin_amdgcn_sched_barrier(0);
-            dq = mfma32(ka[ks % RING], db[ks % RING], dq);
-            if (ks + RING < KSC) rd(ks + RING, &ka[ks % RING], &db[ks % RING]);
+            dq = mfma32(fq[ks % RING], fo[ks % RING], dq);
+            if (ks + RING < KSC) {
+              fq[ks % RING] = rd_kt(ks + RING);
+              fo[ks % RING] = rd_ds(ks + RING);
+            }
           }
           __builtin_amdgcn_sched_barrier(0);
         }
