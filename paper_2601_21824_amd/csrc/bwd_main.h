@@ -294,24 +294,33 @@ __global__ __launch_bounds__(256) void bwd_main_kernel(BwdArgs a) {
       // keep that interleaving.
       //
       // S = Q K^T, dP = dO V^T for query half qb and this wave's 32 keys:
-      // A = Q / dO rows from LDS (RING - 1 k-steps ahead), B = K / V rows
-      // from registers.
-      auto sdp = [&](int qb, auto&& extra) {
-        constexpr int RING = 4;
-        bf16x8 rq[RING], ro[RING];
-        auto rd = [&](int ks) {
-          const int at = bf_at<D>(32 * qb + lc, 16 * ks + 8 * g);
-          rq[ks % RING] = *(const bf16x8*)&qs[at];
-          ro[ks % RING] = *(const bf16x8*)&dos[at];
-        };
+      // A = Q / dO rows from LDS, B = K / V rows from registers.  The LDS
+      // operands of all four runs go through one ring, read AHEAD slots early:
+      // a run's last slots read the next run's first operands (next), so
+      // that no run starts by waiting for LDS (before -> now, us: 16 heads of 2048
+      // at d = 64 full 136.7 -> 133.1, 64 of 1024 causal 72.0 -> 71.0; 16 of 3001 at
+      // d = 128 causal 184.7 -> 182.7).  (Not in the atomic and partials
+      // variants at d = 128, which have no registers left for it: 33 spills.)
+      constexpr bool kCross = ordered || MODE == kModeNoDq || D == 64;
+      constexpr int RING = 4, AHEAD = 3;
+      static_assert(KS % RING == 0 && 2 * NB % RING == 0, "the ring continues from run to run");
+      bf16x8 fq[RING], fo[RING];
+      auto rd_rows = [&](int qb, int ks) {
+        const int at = bf_at<D>(32 * qb + lc, 16 * ks + 8 * g);
+        fq[ks % RING] = *(const bf16x8*)&qs[at];
+        fo[ks % RING] = *(const bf16x8*)&dos[at];
+      };
+      auto sdp = [&](int qb, auto&& next, auto&& extra) {
+        if (!kCross || qb == 0)
 #pragma unroll
-        for (int k = 0; k < RING - 1; ++k) rd(k);
+          for (int k = 0; k < AHEAD; ++k) rd_rows(qb, k);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-          if (ks + RING - 1 < KS) rd(ks + RING - 1);
+          if (ks + AHEAD < KS) rd_rows(qb, ks + AHEAD);
+          else if constexpr (kCross) next(ks + AHEAD - KS);
           __builtin_amdgcn_sched_barrier(0);
-          s[qb] = mfma32(rq[ks % RING], kreg[ks], s[qb]);
-          dp[qb] = mfma32(ro[ks % RING], vreg[ks], dp[qb]);
+          s[qb] = mfma32(fq[ks % RING], kreg[ks], s[qb]);
+          dp[qb] = mfma32(fo[ks % RING], vreg[ks], dp[qb]);
           extra(ks);
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -366,33 +375,33 @@ __global__ __launch_bounds__(256) void bwd_main_kernel(BwdArgs a) {
       };
       // dV += P^T dO and dK += dS^T Q for query half qb: A = P^T, dS^T from
       // registers, B = dO^T, Q^T by transposed reads of the row-major tiles
-      // (RING - 1 operand pairs ahead)
-      auto dvdk = [&](int qb, auto&& extra) {
-        constexpr int NP = 2 * NB, RING = 3;
-        auto rd = [&](int k, bf16x8* bo, bf16x8* bq) {
-          const int nb = k >> 1, half = k & 1;
-          const int col = 32 * nb + 16 * nh + 4 * (L16 & 3);
-          const int row = 32 * qb + 16 * half + 4 * g + (L16 >> 2);
-          *bo = as_bf16x8(tr_read(&dos[bf_at<D>(row, col)]), tr_read(&dos[bf_at<D>(row + 8, col)]));
-          *bq = as_bf16x8(tr_read(&qs[bf_at<D>(row, col)]), tr_read(&qs[bf_at<D>(row + 8, col)]));
-        };
-        bf16x8 ro[RING], rq[RING];
+      auto rd_cols = [&](int qb, int k) {
+        const int nb = k >> 1, half = k & 1;
+        const int col = 32 * nb + 16 * nh + 4 * (L16 & 3);
+        const int row = 32 * qb + 16 * half + 4 * g + (L16 >> 2);
+        fo[k % RING] = as_bf16x8(tr_read(&dos[bf_at<D>(row, col)]), tr_read(&dos[bf_at<D>(row + 8, col)]));
+        fq[k % RING] = as_bf16x8(tr_read(&qs[bf_at<D>(row, col)]), tr_read(&qs[bf_at<D>(row + 8, col)]));
+      };
+      auto dvdk = [&](int qb, auto&& next, auto&& extra) {
+        constexpr int NP = 2 * NB;
+        if constexpr (!kCross)
 #pragma unroll
-        for (int k = 0; k < RING; ++k) rd(k, &ro[k], &rq[k]);
+          for (int k = 0; k < AHEAD; ++k) rd_cols(qb, k);
 #pragma unroll
         for (int k = 0; k < NP; ++k) {
           __builtin_amdgcn_sched_barrier(0);
           const int nb = k >> 1, half = k & 1;
-          dvacc[nb] = mfma32(pbf[qb][half], ro[k % RING], dvacc[nb]);
-          dkacc[nb] = mfma32(dsbf[qb][half], rq[k % RING], dkacc[nb]);
-          if (k + RING < NP) rd(k + RING, &ro[k % RING], &rq[k % RING]);
+          dvacc[nb] = mfma32(pbf[qb][half], fo[k % RING], dvacc[nb]);
+          dkacc[nb] = mfma32(dsbf[qb][half], fq[k % RING], dkacc[nb]);
+          if (k + AHEAD < NP) rd_cols(qb, k + AHEAD);
+          else if constexpr (kCross) next(k + AHEAD - NP);
           extra(k);
         }
         __builtin_amdgcn_sched_barrier(0);
       };
 
       // run 1: S/dP of half 0, with the next block's Q / dO / L / D prefetch
-      sdp(0, [&](int ks) {
+      sdp(0, [&](int k) { rd_rows(1, k); }, [&](int ks) {
         if (pb_next < 0) return;
         if (ks < QLD) load_part(pb_next, buf ^ 1, ks);
         if (ks == 0) load_ld(pb_next, buf ^ 1);
@@ -416,7 +425,7 @@ __global__ __launch_bounds__(256) void bwd_main_kernel(BwdArgs a) {
       const bool early_acc = ordered && have_turn && rank > 0;
       read_ld(0, 0);
       // run 2: S/dP of half 1, with softmax of half 0 and the accumulator fetch
-      sdp(1, [&](int ks) {
+      sdp(1, [&](int k) { rd_cols(0, k); }, [&](int ks) {
 #pragma unroll
         for (int p = ks * 8 / KS; p < (ks + 1) * 8 / KS; ++p) {
           softmax_piece(0, p);
@@ -436,12 +445,12 @@ __global__ __launch_bounds__(256) void bwd_main_kernel(BwdArgs a) {
         release();
       }
       // run 3: dV/dK of half 0, with softmax of half 1
-      dvdk(0, [&](int k) {
+      dvdk(0, [&](int k) { rd_cols(1, k); }, [&](int k) {
 #pragma unroll
         for (int p = k * 8 / (2 * NB); p < (k + 1) * 8 / (2 * NB); ++p) softmax_piece(1, p);
       });
       // run 4: dV/dK of half 1, with the dS^T stores
-      dvdk(1, [&](int k) {
+      dvdk(1, [](int) {}, [&](int k) {
         if constexpr (MODE != kModeNoDq) {
 #pragma unroll
           for (int p = k * 8 / (2 * NB); p < (k + 1) * 8 / (2 * NB); ++p) store_ds_piece(p);
