@@ -88,6 +88,96 @@ __device__ inline u32x2 lds_tr(uint32_t at) {
   return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(at)));
 }
 
+// A wave's rows whose running maximum (log2 domain) is this far from 0, or -inf
+// after the first unit, go through far_rows.
+constexpr float kFarMax = 1048576.f;
+
+// Rows row0 .. row0 + 31 by one wave from global memory, for rows the pipelined loop
+// cannot do: it takes S c2 - m in one fused operation, which for the largest
+// score is not 0 but the error of m's own rounding, up to 2^-24 |m|, and 2^that
+// overflows from |m| = 2^31 on (keys taken out by an added -1e30, for a row that
+// has seen no other yet); and it takes -inf less -inf after 32 keys that all score
+// -inf.  Here S c2 is rounded as m was, so that the largest score gives
+// P = 1, and keys that score -inf have P = 0 (a row of nothing else: O NaN, L -inf).
+// Not tuned, and small: 64 columns of O a pass, each pass with its own scores, V's
+// operands gathered two bytes at a time, nothing kept in registers through the
+// loop for it (O of 256 columns at once cost the loop of d = 256 3-6%).  Its rows
+// cost 2 (d = 64) to 7 (d = 256) times the loop's; taking m off inside the loop
+// instead, where it is far, cost every call 2-7%.
+template <int D>
+__device__ void far_rows(const FwdArgs& a, int bh, int row0) {
+  const int l = fresh_lane();
+  const int N = a.n, g = l >> 5, lc = l & 31, qrow = row0 + lc;
+  const float c2 = a.scale * kLog2e;
+  const size_t head = (size_t)bh * N * D;
+  const uint32_t hbytes = (uint32_t)((size_t)N * D * 2);
+  const auto rq = make_rsrc((const __bf16*)a.q + head, hbytes);
+  const auto rk = make_rsrc((const __bf16*)a.k + head, hbytes);
+  const auto rv = make_rsrc((const __bf16*)a.v + head, hbytes);
+  const auto ro = make_rsrc((__bf16*)a.o + head, hbytes);
+  const int end = a.causal ? min(N, row0 + 32) : N;
+#pragma clang loop unroll(disable)
+  for (int d0 = 0; d0 < D; d0 += 64) {
+    f32x16 o[2];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[0][r] = o[1][r] = 0.f;
+    float m = -INFINITY, sum = 0.f;
+#pragma clang loop unroll(disable)
+    for (int k0 = 0; k0 < end; k0 += 32) {
+      f32x16 s;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma clang loop unroll(disable)
+      for (int c = 0; c < D; c += 16)
+        s = mfma32(as_bf16x8(ld16(rk, (uint32_t)((k0 + lc) * D + c + 8 * g) * 2)),
+                   as_bf16x8(ld16(rq, (uint32_t)(qrow * D + c + 8 * g) * 2)), s);
+      // element r: key k0 + 8(r/4) + 4g + r%4, query qrow
+      const int lim = (a.causal ? min(N - 1, qrow) : N - 1) - k0 - 4 * g;
+      float mx = -INFINITY;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        float x = s[r] * c2;
+        asm("" : "+v"(x));  // rounded: not to be fused with the difference
+        s[r] = 8 * (r >> 2) + (r & 3) > lim ? -INFINITY : x;
+        mx = fmaxf(mx, s[r]);
+      }
+      const float mnew = fmaxf(m, half_max(mx));
+      const float mm = mnew == -INFINITY ? 0.f : mnew;
+      const float alpha = __builtin_amdgcn_exp2f(m - mm);
+      m = mnew;
+      float rs = 0.f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) rs += s[r] = __builtin_amdgcn_exp2f(s[r] - mm);
+      sum = sum * alpha + half_sum(rs);
+#pragma unroll
+      for (int db = 0; db < 2; ++db) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          unsigned e[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            e[i] = ld2(rv, (uint32_t)((k0 + 16 * h + 8 * (i >> 2) + 4 * g + (i & 3)) * D + d0 + 32 * db + lc) * 2);
+          const u32x4 v = {e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16};
+          o[db] = mfma32(as_bf16x8(v), pack8(s, 8 * h), o[db]);
+        }
+      }
+    }
+    const float inv = 1.f / sum;
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+      for (int rb = 0; rb < 4; ++rb) {
+        const u32x2 t = {pack_bf16(o[db][4 * rb] * inv, o[db][4 * rb + 1] * inv),
+                         pack_bf16(o[db][4 * rb + 2] * inv, o[db][4 * rb + 3] * inv)};
+        st8(ro, (uint32_t)(qrow * D + d0 + 32 * db + 8 * rb + 4 * g) * 2, t);
+      }
+    if (d0 == 0 && g == 0)
+      st4f(make_rsrc(a.lse + (size_t)bh * N, (uint32_t)N * 4), (uint32_t)qrow * 4, (m + __log2f(sum)) * kLn2);
+  }
+}
+
 template <int D, int QG, int WPS>
 __global__ __launch_bounds__(256, WPS) void attn_fwd_kernel(FwdArgs a) {
   constexpr int KT = D == 256 ? 32 : 64;  // keys per tile
@@ -394,6 +484,12 @@ __global__ __launch_bounds__(256, WPS) void attn_fwd_kernel(FwdArgs a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) max_piece(s[0], qg, i);
   rescale();
+  // a row's maximum only rises: where it starts and where it ends say whether it
+  // was ever far from 0 (a row of NaN scores is done as any other)
+  bool far = false;
+#pragma unroll
+  for (int qg = 0; qg < QG; ++qg) far |= !(m[qg] > -kFarMax) && mx[qg] == mx[qg];
+  const bool far_first = __any(far);
   if (NU == 1) {
     published = 1;
     publish(1);
@@ -426,6 +522,14 @@ __global__ __launch_bounds__(256, WPS) void attn_fwd_kernel(FwdArgs a) {
   pv(0, [&](int p, int qg) { b_slot(s[0], s[0], p * QG + qg, false); });
   // the other waves' remaining tiles
   for (int t = published + 1; t < nt; ++t) publish(t);
+
+#pragma unroll
+  for (int qg = 0; qg < QG; ++qg) far = (qg > 0 && far) || m[qg] >= kFarMax;
+  if (far_first || __any(far)) {
+    for (int qg = 0; qg < QG; ++qg)
+      if (q0w + 32 * qg < N) far_rows<D>(a, bh, q0w + 32 * qg);
+    return;
+  }
 
   // oacc[qg][db][r] <-> d = 32db + 8(r/4) + 4g + r%4, query q0w + 32qg + lc
   const auto ro = make_rsrc((__bf16*)a.o + head, hbytes);

@@ -61,3 +61,43 @@ def test_nan_keys_reach_only_rows_that_see_them():
     o, lse = dash.attn_fwd(q, k, v, True)
     assert not o[0, 0].isnan().any() and not o[0, 1, :100].isnan().any() and not lse[0, 1, :100].isnan().any()
     assert o[0, 1, 100:].isnan().all() and lse[0, 1, 100:].isnan().all()
+
+
+# (leading keys, what is added to their scores / sqrt(d)): rows of a full mask see
+# other keys after them; causal rows before them see no other
+FAR = [(n, s) for n in (20, 32, 40, 64, 130) for s in (-1e4, -3e9, -1e30, float("-inf"))]
+
+
+@pytest.mark.parametrize("lead,shift", FAR)
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("heads,d", [(2, 64), (512, 64), (2, 128), (2, 256)])
+def test_leading_keys_far_below_the_others(heads, d, causal, lead, shift):
+    """Keys taken out of the softmax by a large negative score (left padding by an
+    extra channel) ahead of those that count: whole units of 32 keys, and half
+    ones, whose row maximum is that score.  Against the definition in float64 where it
+    is defined (a causal row whose keys all score -inf has none: O is NaN)."""
+    N = 200
+    g = torch.Generator(device="cuda")
+    g.manual_seed(lead + d)
+    q, k, v = (torch.randn((1, heads, N, d), generator=g, device="cuda").bfloat16() for _ in range(3))
+    q[..., 0] = 1
+    k[:, :, :lead, 0] = shift
+    o, lse = dash.attn_fwd(q, k, v, causal)
+    some = [0, heads - 1]
+    s = q[0, some].double() @ k[0, some].double().transpose(1, 2).contiguous() / math.sqrt(d)
+    if causal:
+        s.masked_fill_(torch.ones((N, N), dtype=torch.bool, device="cuda").triu(1), float("-inf"))
+    ro, rl = torch.softmax(s, -1) @ v[0, some].double(), torch.logsumexp(s, -1)
+    o, lse = o[0, some].double(), lse[0, some].double()
+    ok = ro.isfinite().all(-1)
+    assert int(ok.sum()) == (2 * (N - lead) if causal and math.isinf(shift) else 2 * N)
+    assert o[~ok].isnan().all()
+    # rows that see only shifted keys: their scores are shift + O(1) in fp32, whose
+    # spacing beside shift (2^-23 |shift|) is the error of a score
+    if causal and shift == -3e9:
+        ok &= torch.arange(N, device="cuda") >= lead
+    err = (o[ok] - ro[ok]).abs()
+    assert float(err.norm() / ro[ok].norm()) <= REL_FROB
+    assert float(err.max() / ro[ok].abs().max()) <= REL_MAX
+    assert o.isfinite().all(-1).equal(ro.isfinite().all(-1))
+    assert bool(((lse[ok] - rl[ok]).abs() <= 2e-5 * rl[ok].abs().clamp(min=1)).all())
