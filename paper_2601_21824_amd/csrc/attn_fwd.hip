@@ -562,12 +562,14 @@ hipError_t launch_attn_fwd(const FwdArgs& a, int d, hipStream_t stream) {
   // workgroups enough for two per CU, and under a causal mask leave half of a
   // diagonal workgroup's waves waiting.  At d = 64, full mask, 512 to 4096
   // such workgroups: 0-11% faster (16 heads of 8192: 291 against 322 us), with
-  // 256 and fewer 1-33% slower, causal 3-34% slower below N = 16384.  At d = 128 two groups leave
-  // room for one wave per SIMD only: -13% to +4% at 512 workgroups and more,
-  // so it is not built.
+  // 256 and fewer 1-33% slower, causal 3-34% slower below N = 16384.  A head of at most 128 rows
+  // leaves two of the four waves without any: 600 heads of 100 13.8 us against
+  // 9.1, 2048 of 128 34.2 against 29.7, 8192 of 33 61.8 against 37.1.  At d = 128 two
+  // groups leave room for one wave per SIMD only: -13% to +4% at 512 workgroups
+  // and more, so it is not built.
   const long wide = (long)((a.n + 255) / 256) * a.bh;
   if (d == 64) {
-    if (!a.causal && wide >= 512) launch_fwd<64, 2, 2>(a, stream);
+    if (!a.causal && a.n > 128 && wide >= 512) launch_fwd<64, 2, 2>(a, stream);
     else launch_fwd<64, 1, 3>(a, stream);
   } else if (d == 128) {
     launch_fwd<128, 1, 2>(a, stream);

@@ -14,9 +14,9 @@ pytestmark = pytest.mark.gpu
 
 LENGTHS = (1, 31, 32, 33, 63, 64, 65, 96, 127, 129, 255, 257, 300, 513)
 # (heads, N, d, causal): every length at a head count that the XCD count does
-# not divide and one that it does; then d = 64 full calls at the two-group rule
+# not divide and one that it does; then d = 64 full calls at the two-group rule (N > 128 and 512 workgroups of 256 rows)
 CASES = [(h, n, d, c) for d in (64, 128, 256) for c in (False, True) for n in LENGTHS for h in (3, 8)]
-CASES += [(512, 100, 64, False), (511, 250, 64, False), (171, 520, 64, False), (170, 520, 64, False), (520, 33, 64, True)]
+CASES += [(512, 100, 64, False), (512, 128, 64, False), (512, 129, 64, False), (511, 250, 64, False), (171, 520, 64, False), (170, 520, 64, False), (520, 33, 64, True)]
 
 
 @pytest.mark.parametrize("heads,N,d,causal", CASES)
