@@ -312,8 +312,10 @@ int dash_mfma_peak(int iters, double* tflops);
  * d = 64 and 128 and 64 at d = 256, and twice that when the call has tiles of
  * that size enough over all heads: at least 256 at d = 64 (causal: 512 and
  * N >= 1024), 160 at d = 128 (causal: 384 and N > 256), 128 at d = 256 (causal:
- * 192; more than one head); at d = 128 and 256 not for ATOMIC and SPLIT -- so
- * the summation order depends on the call's number of heads,
+ * 192; more than one head); at d = 128, and below N = 512 at d = 256, only where that
+ * also saves enough rounds of 256 chains (kv_tile_rows in csrc/schedule.h), and
+ * at d = 128 and 256 not for ATOMIC and SPLIT.  The summation order, and so a head's
+ * bits, therefore depend on the call's number of heads.  The view is that
  * under `placement` (DASH_PLACEMENT_GLOBAL or DASH_PLACEMENT_XCD; only
  * Shift's groups depend on it).  Writes, when the pointer is non-NULL:
  *   geometry[6]            = {T_r, T_c, br, number of workgroup chains per

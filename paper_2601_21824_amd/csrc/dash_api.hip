@@ -72,7 +72,7 @@ Layout layout(int B, int H, int N, int d, int sched) {
   // tiles (half the chains) is the smaller one, so that the size is the narrow
   // tiles' wherever a call may take either.
   size_t chains = 0, entries = 0;
-  for (int s : {(int)dash::S_SHIFT, (int)dash::S_SPLIT})
+  for (int s : {(int)dash::S_SHIFT, (int)dash::S_NAIVE, (int)dash::S_SPLIT})
     for (int c = 0; c < 2; ++c) {
       const dash::Geom G = dash::make_geom(s == dash::S_SHIFT && c ? dash::S_SYMSHIFT : s, c, N, d, (long)bh);
       const size_t n = (size_t)G.t_c + 1;

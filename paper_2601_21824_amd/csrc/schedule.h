@@ -64,20 +64,45 @@ struct Geom {
   int chain_major;  // work tickets chain-major (see ticket_chain), else head-major
 };
 
+// Time of a call with KV tiles of bc rows, in steps of one such tile, on 256
+// workgroups that run one chain at a time.  Chains of one length (full mask: a tile
+// each; Symmetric Shift: two tiles each) run in whole rounds.  The uneven chains of
+// the other causal orders fill a round's end with the next one's start: the mean
+// of whole rounds and the work's share, and no less than the longest chain; `start`
+// is what beginning a tile costs there.
+DASH_HD double tile_steps(int sched, int causal, int N, long heads, int bc, double start) {
+  const long nb = (N + kBlockRows - 1) / kBlockRows, t = (N + bc - 1) / bc;
+  auto rounds = [](long chains) { return (double)((chains + 255) / 256); };
+  if (!causal) return rounds(heads * t) * (double)nb;
+  const double sum = (double)(t * nb - bc / kBlockRows * (t * (t - 1) / 2));  // of a head's chains
+  if (sched == S_SYMSHIFT) return rounds(heads * ((t + 1) / 2)) * sum / (double)((t + 1) / 2);
+  const double share = (double)(heads * t) / 256.0;
+  const double all = 0.5 * (rounds(heads * t) + share) * (sum / (double)t + start), longest = (double)nb + start;
+  return all > longest ? all : longest;
+}
+
 // rows per KV tile.  Every head dim has a narrow and a wide tile: 128 and 256
 // rows at d = 64 and 128, 64 and 128 at d = 256.  The wide one halves the
-// accumulator traffic per FLOP and is 1.1-1.9 times faster per FLOP, but a call
-// needs tiles enough to fill a 256-CU GPU, whose workgroups run one tile each:
+// accumulator traffic per FLOP and is 1.2-2 times faster per FLOP on a full GPU, but a
+// call needs tiles enough to fill a 256-CU GPU, whose workgroups run one tile each,
+// and tiles that N fills:
 //  d = 64   256 wide tiles over all heads; causal (uneven chains) 512 and
 //           N >= 1024.
-//  d = 128  160 (narrow / wide time: 128 tiles 0.75-0.84, 192 tiles 1.23, 256
-//           tiles 1.16-1.30, 512 and more 1.14-1.28); causal 384 and N > 256
-//           (256 tiles 0.84-0.98, 384 tiles 1.23, 512 and more 1.06-1.28; N = 256
-//           0.99 at 512 tiles).
-//  d = 256  128 (64 tiles 0.97-1.11, 128 tiles 1.03-1.25, 256 and more 1.40-1.99);
-//           causal 192 (128 tiles 0.87-1.07, 192 tiles 1.18, 256 and more
-//           1.20-1.88); a call of one head keeps the narrow tile, whose Shift
-//           groups at N = 32768 are its documented geometry.
+//  d = 128  160 (narrow / wide time: 64-127 tiles 0.67-0.84, 128-159 tiles 0.73-1.26,
+//           192 and more, where the rule below takes them, 1.05-1.3); causal 384
+//           and N > 256 (128-255 tiles 0.65-1.0, 256-383 tiles 0.64-1.24).
+//  d = 256  128 (32-95 tiles 0.74-1.17, 96-127 tiles 0.75-1.21, 256 and more at N >=
+//           512 1.4-2); causal 192 (48-127 tiles 0.73-1.06, 128-191 tiles
+//           0.78-1.16).  A call of one head keeps the narrow tile, although the
+//           wide one measured 1.4 (Shift 2.0) times faster full from N = 16257
+//           on and 0.95-1.4 causal from N = 24449: it is the only call whose Shift
+//           order has more than one group of kMaxGroup chains.
+// At d = 128, and at d = 256 below N = 512, the narrow tiles besides have to take more
+// than 1.5 (causal Naive and Descending 1.45; d = 256: 1.2) times as many steps
+// (tile_steps), which is what a wide step takes of a narrow one's time.  Heads of
+// a few tiles and a last round that few wide tiles begin do not: 264 heads of
+// 128 full at d = 128 35.5 us narrow, 52.0 wide; 9 of 8192 1299 and 1440; 264 of 128
+// causal at d = 256 55.2 and 81.9.
 // The atomic variant and SPLIT's dK, dV pass (no ordered accumulator) exist for
 // the narrow tile only at d = 128 and 256.  The tile size is part of the
 // summation order, so it is a function of the problem (schedule, d, mask, N,
@@ -90,6 +115,10 @@ DASH_HD int kv_tile_rows(int sched, int d, int causal, int N, long heads) {
   else if (sched == S_ATOMIC || sched == S_SPLIT) w = false;
   else if (d == 128) w = causal ? (N > 256 && wide >= 384) : wide >= 160;
   else w = heads > 1 && wide >= (causal ? 192 : 128);
+  if (w && (d == 128 || (d == 256 && N < 512))) {
+    const double step = d == 256 ? 1.2 : causal && sched != S_SYMSHIFT ? 1.45 : 1.5;
+    w = tile_steps(sched, causal, N, heads, narrow, 0.5) > step * tile_steps(sched, causal, N, heads, 2 * narrow, 1.0);
+  }
   return w ? 2 * narrow : narrow;
 }
 

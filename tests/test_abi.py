@@ -99,6 +99,67 @@ KINDS = {b.DASH_SCHED_NAIVE: osched.NAIVE, b.DASH_SCHED_DESCENDING: osched.DESCE
          b.DASH_SCHED_SPLIT: osched.NAIVE}
 
 
+def tile_rows(sched, d, causal, N, heads):
+    """KV tile rows: narrow (128; 64 at d = 256), or twice that when the call has
+    tiles enough for 256 workgroups and, at d = 128 and below N = 512 at d = 256, the
+    narrow ones take enough more rounds of 256 chains."""
+    bc = 64 if d == 256 else 128
+    if d != 64 and sched in (b.DASH_SCHED_ATOMIC, b.DASH_SCHED_SPLIT):
+        return bc
+    tiles = heads * -(-N // (2 * bc))
+    if tiles < {64: (256, 512), 128: (160, 384), 256: (128, 192)}[d][causal]:
+        return bc
+    if causal and N < {64: 1024, 128: 257, 256: 0}[d] or d == 256 and heads == 1:
+        return bc
+    if d == 64 or d == 256 and N >= 512:
+        return 2 * bc
+
+    def time(rows, start):
+        chains = [-(-N // 64) - (j * rows // 64 if causal else 0) for j in range(-(-N // rows))]
+        if sched == b.DASH_SCHED_SYMSHIFT:
+            chains = [sum(chains) / -(-len(chains) // 2)] * -(-len(chains) // 2)
+        n = heads * len(chains)
+        rounds, mean = -(-n // 256), sum(chains) / len(chains)
+        if not causal or sched == b.DASH_SCHED_SYMSHIFT:
+            return rounds * mean
+        return max((rounds + n / 256) / 2 * (mean + start), chains[0] + start)
+
+    step = 1.2 if d == 256 else 1.45 if causal and sched != b.DASH_SCHED_SYMSHIFT else 1.5
+    return 2 * bc if time(bc, 0.5) > step * time(2 * bc, 1.0) else bc
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("causal", [False, True])
+def test_tile_rows_of_many_calls(d, causal):
+    """The tile size of the library's tables over heads and lengths of every kind."""
+    rng = np.random.default_rng(d + causal)
+    seen = set()
+    for _ in range(400):
+        N, heads = int(2 ** rng.uniform(4, 13)), int(2 ** rng.uniform(0, 11))
+        for s in (0, 1, 2, 4 if causal else 3, 6, 7):
+            bc = b.dash_schedule_table(s, N, d, causal, heads=heads)["bc"]
+            assert bc == tile_rows(s, d, causal, N, heads), (s, N, heads)
+            seen.add(bc)
+    assert len(seen) == 2
+
+
+# (schedule, heads, N, d, causal, rows): the faster tile, both measured.  Short heads and
+# a last round that few wide tiles begin: narrow (the wide one took 1.06-1.6 times as long)
+FASTER = [("shift", 264, 64, 128, False, 128), ("shift", 264, 128, 128, False, 128), ("naive", 264, 200, 128, False, 128),
+          ("shift", 132, 300, 128, False, 128), ("shift", 9, 8192, 128, False, 128), ("shift", 20, 4096, 128, False, 128),
+          ("descending", 200, 300, 128, True, 128), ("symshift", 37, 3328, 128, True, 128), ("symshift", 162, 960, 128, True, 128),
+          ("shift", 1024, 64, 256, False, 64), ("shift", 128, 128, 256, False, 64), ("symshift", 264, 64, 256, True, 64),
+          ("descending", 264, 97, 256, True, 64),
+          ("shift", 32, 8192, 128, False, 256), ("symshift", 64, 8192, 128, True, 256), ("descending", 64, 8192, 128, True, 256),
+          ("shift", 256, 256, 128, False, 256), ("descending", 1024, 512, 128, True, 256), ("descending", 8, 32768, 256, True, 128),
+          ("symshift", 8, 32768, 256, True, 128), ("shift", 33, 900, 256, False, 128), ("descending", 25, 1280, 256, True, 128)]
+
+
+@pytest.mark.parametrize("sched,heads,N,d,causal,rows", FASTER)
+def test_calls_take_the_faster_tile(sched, heads, N, d, causal, rows):
+    assert b.dash_schedule_table(sched, N, d, causal, heads=heads)["bc"] == rows
+
+
 @pytest.mark.parametrize("placement", [b.DASH_PLACEMENT_GLOBAL, b.DASH_PLACEMENT_XCD])
 @pytest.mark.parametrize("d", [64, 128, 256])
 @pytest.mark.parametrize("N", [64, 200, 256, 1000, 1024, 4096, 4224, 8192, 16384, 32768])
@@ -108,20 +169,13 @@ KINDS = {b.DASH_SCHED_NAIVE: osched.NAIVE, b.DASH_SCHED_DESCENDING: osched.DESCE
 def test_schedule_table_matches_oracle(heads, sched, causal, N, d, placement):
     if sched == b.DASH_SCHED_SYMSHIFT and not causal:
         pytest.skip("symshift is causal-only")
-    if heads > 1 and d != 64:
-        pytest.skip("the head count decides the tile size at d = 64 only")
     tab = b.dash_schedule_table(sched, N, d, causal, placement, heads=heads)
     concrete = b.dash_resolve_schedule(sched, d, causal)
     kind = KINDS[concrete]
     t_r, t_c, br, bc, grp = tab["t_r"], tab["t_c"], tab["br"], tab["bc"], tab["group"]
-    # tile sizes: KV tiles of 128 rows at d = 128, 64 at d = 256, and at d = 64
-    # 256 rows when the call has enough of them (full: 256 over all heads;
-    # causal: 512 and N >= 1024), else 128; Q tiles of 64 rows (full) or
-    # KV-tile rows (causal); Shift groups of at most 256 chains, 32 when every
-    # chain of a head runs on one XCD
-    wide = heads * -(-N // 256)
-    bc64 = 256 if ((N >= 1024 and wide >= 512) if causal else wide >= 256) else 128
-    assert bc == {64: bc64, 128: 128, 256: 64}[d]
+    # Q tiles of 64 rows (full) or KV-tile rows (causal); Shift groups of at
+    # most 256 chains, 32 when every chain of a head runs on one XCD
+    assert bc == tile_rows(concrete, d, causal, N, heads)
     assert br == (bc if causal else 64) and t_r * br == t_c * bc
     most = 32 if placement == b.DASH_PLACEMENT_XCD else 256
     assert grp == (min(t_c, most) if kind == osched.SHIFT else tab["chains"])
