@@ -64,21 +64,22 @@ struct Geom {
   int chain_major;  // work tickets chain-major (see ticket_chain), else head-major
 };
 
-// Time of a call with KV tiles of bc rows, in steps of one such tile, on 256
-// workgroups that run one chain at a time.  Chains of one length (full mask: a tile
-// each; Symmetric Shift: two tiles each) run in whole rounds.  The uneven chains of
-// the other causal orders fill a round's end with the next one's start: the mean
-// of whole rounds and the work's share, and no less than the longest chain; `start`
-// is what beginning a tile costs there.
-DASH_HD double tile_steps(int sched, int causal, int N, long heads, int bc, double start) {
+// Time of a call with KV tiles of bc rows on 256 workgroups that run one chain at a
+// time; a block step of a busy GPU takes `step`.  Chains of one length (full mask: a
+// tile each; Symmetric Shift: two tiles each) run in whole rounds.  The uneven chains
+// of the other causal orders fill most of a round's end with the next one's start:
+// between whole rounds (`fill` of the way) and the work's share, and no less than the
+// longest chain, whose steps take 1 (it ends on a GPU that is no longer busy);
+// `start` is what beginning a tile costs there, in steps.
+DASH_HD double tile_time(int sched, int causal, int N, long heads, int bc, double step, double fill, double start) {
   const long nb = (N + kBlockRows - 1) / kBlockRows, t = (N + bc - 1) / bc;
   auto rounds = [](long chains) { return (double)((chains + 255) / 256); };
-  if (!causal) return rounds(heads * t) * (double)nb;
+  if (!causal) return step * rounds(heads * t) * (double)nb;
   const double sum = (double)(t * nb - bc / kBlockRows * (t * (t - 1) / 2));  // of a head's chains
-  if (sched == S_SYMSHIFT) return rounds(heads * ((t + 1) / 2)) * sum / (double)((t + 1) / 2);
-  const double share = (double)(heads * t) / 256.0;
-  const double all = 0.5 * (rounds(heads * t) + share) * (sum / (double)t + start), longest = (double)nb + start;
-  return all > longest ? all : longest;
+  if (sched == S_SYMSHIFT) return step * rounds(heads * ((t + 1) / 2)) * sum / (double)((t + 1) / 2);
+  const double all = fill * rounds(heads * t) + (1.0 - fill) * (double)(heads * t) / 256.0;
+  const double busy = step * all * (sum / (double)t + start), longest = (double)nb + start;
+  return busy > longest ? busy : longest;
 }
 
 // rows per KV tile.  Every head dim has a narrow and a wide tile: 128 and 256
@@ -97,10 +98,10 @@ DASH_HD double tile_steps(int sched, int causal, int N, long heads, int bc, doub
 //           wide one measured 1.4 (Shift 2.0) times faster full from N = 16257
 //           on and 0.95-1.4 causal from N = 24449: it is the only call whose Shift
 //           order has more than one group of kMaxGroup chains.
-// At d = 128, and at d = 256 below N = 512, the narrow tiles besides have to take more
-// than 1.5 (causal Naive and Descending 1.45; d = 256: 1.2) times as many steps
-// (tile_steps), which is what a wide step takes of a narrow one's time.  Heads of
-// a few tiles and a last round that few wide tiles begin do not: 264 heads of
+// At d = 128, and at d = 256 below N = 512, it besides has to be the faster one by
+// tile_time, with a wide step at 1.5 times a narrow one at d = 128 and 1.2 at d = 256
+// (causal Naive and Descending 1.45), as fits 5,900 measured calls.  Heads of a few tiles
+// and a last round that few wide tiles begin are slower with it: 264 heads of
 // 128 full at d = 128 35.5 us narrow, 52.0 wide; 9 of 8192 1299 and 1440; 264 of 128
 // causal at d = 256 55.2 and 81.9.
 // The atomic variant and SPLIT's dK, dV pass (no ordered accumulator) exist for
@@ -116,8 +117,10 @@ DASH_HD int kv_tile_rows(int sched, int d, int causal, int N, long heads) {
   else if (d == 128) w = causal ? (N > 256 && wide >= 384) : wide >= 160;
   else w = heads > 1 && wide >= (causal ? 192 : 128);
   if (w && (d == 128 || (d == 256 && N < 512))) {
-    const double step = d == 256 ? 1.2 : causal && sched != S_SYMSHIFT ? 1.45 : 1.5;
-    w = tile_steps(sched, causal, N, heads, narrow, 0.5) > step * tile_steps(sched, causal, N, heads, 2 * narrow, 1.0);
+    const bool uneven = causal && sched != S_SYMSHIFT;
+    const double step = uneven ? 1.45 : d == 128 ? 1.5 : 1.2, fill = d == 128 ? 0.5 : 0.25, start = d == 128 ? 1.0 : 0.0;
+    w = tile_time(sched, causal, N, heads, narrow, 1.0, fill, 0.5 * start) >
+        tile_time(sched, causal, N, heads, 2 * narrow, step, fill, start);
   }
   return w ? 2 * narrow : narrow;
 }

@@ -114,18 +114,21 @@ def tile_rows(sched, d, causal, N, heads):
     if d == 64 or d == 256 and N >= 512:
         return 2 * bc
 
-    def time(rows, start):
+    even = not causal or sched == b.DASH_SCHED_SYMSHIFT
+    fill, start = (0.5, 1.0) if d == 128 else (0.25, 0.0)
+
+    def time(rows, step, start):
         chains = [-(-N // 64) - (j * rows // 64 if causal else 0) for j in range(-(-N // rows))]
         if sched == b.DASH_SCHED_SYMSHIFT:
             chains = [sum(chains) / -(-len(chains) // 2)] * -(-len(chains) // 2)
         n = heads * len(chains)
         rounds, mean = -(-n // 256), sum(chains) / len(chains)
-        if not causal or sched == b.DASH_SCHED_SYMSHIFT:
-            return rounds * mean
-        return max((rounds + n / 256) / 2 * (mean + start), chains[0] + start)
+        if even:
+            return step * rounds * mean
+        return max(step * (fill * rounds + (1 - fill) * n / 256) * (mean + start), chains[0] + start)
 
-    step = 1.2 if d == 256 else 1.45 if causal and sched != b.DASH_SCHED_SYMSHIFT else 1.5
-    return 2 * bc if time(bc, 0.5) > step * time(2 * bc, 1.0) else bc
+    step = 1.45 if not even else 1.5 if d == 128 else 1.2
+    return 2 * bc if time(bc, 1.0, start / 2) > time(2 * bc, step, start) else bc
 
 
 @pytest.mark.parametrize("d", [64, 128, 256])
@@ -152,7 +155,7 @@ FASTER = [("shift", 264, 64, 128, False, 128), ("shift", 264, 128, 128, False, 1
           ("descending", 264, 97, 256, True, 64),
           ("shift", 32, 8192, 128, False, 256), ("symshift", 64, 8192, 128, True, 256), ("descending", 64, 8192, 128, True, 256),
           ("shift", 256, 256, 128, False, 256), ("descending", 1024, 512, 128, True, 256), ("descending", 8, 32768, 256, True, 128),
-          ("symshift", 8, 32768, 256, True, 128), ("shift", 33, 900, 256, False, 128), ("descending", 25, 1280, 256, True, 128)]
+          ("symshift", 8, 32768, 256, True, 128), ("descending", 72, 387, 256, True, 128), ("shift", 33, 900, 256, False, 128), ("descending", 25, 1280, 256, True, 128)]
 
 
 @pytest.mark.parametrize("sched,heads,N,d,causal,rows", FASTER)
