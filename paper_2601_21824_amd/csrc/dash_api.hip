@@ -282,10 +282,22 @@ bool auto_chain_major(int sched, int causal, int d, long chains, long resident, 
 // length N, interpolated log-linearly between the calibrated shapes (first in
 // the number of heads at the two calibrated lengths around N, then in N) and
 // held constant beyond them; < 0 when nothing was calibrated at (d, mask).
-double step_us_at(int d, int causal, int sched, int n, long heads) {
+// Only shapes that take the call's KV tile count: a step is 64 queries against a
+// tile, so that a wide one is twice the work, and between a narrow and a wide
+// shape the time does not run along a line but steps where the tile changes (5 heads of
+// 8192 full at d = 128 would get 4.5 us for wide steps of 6.4).
+struct StepKey {
+  int d, causal, sched, bc;  // bc: rows per KV tile (0: any)
+  bool takes(const dash::StepCost& e) const {
+    return e.d == d && e.causal == causal && e.sched == sched &&
+           (bc == 0 || dash::kv_tile_rows(sched, d, causal, e.n, e.heads) == bc);
+  }
+};
+
+double step_us_at(const StepKey& key, int n, long heads) {
   double h0 = -1, u0 = 0, h1 = -1, u1 = 0;  // nearest calibrated head counts below / above
   for (const dash::StepCost& e : dash::kStepCosts) {
-    if (e.d != d || e.causal != causal || e.sched != sched || e.n != n) continue;
+    if (e.n != n || !key.takes(e)) continue;
     if (e.heads <= heads && (h0 < 0 || e.heads > h0)) h0 = e.heads, u0 = e.us;
     if (e.heads >= heads && (h1 < 0 || e.heads < h1)) h1 = e.heads, u1 = e.us;
   }
@@ -296,18 +308,22 @@ double step_us_at(int d, int causal, int sched, int n, long heads) {
 }
 
 double step_us(int d, int causal, int sched, int N, long heads) {
-  double n0 = -1, n1 = -1;  // nearest calibrated lengths at or below / at or above N
-  for (const dash::StepCost& e : dash::kStepCosts) {
-    if (e.d != d || e.causal != causal || e.sched != sched || e.n <= 0) continue;
-    if (e.n <= N && (n0 < 0 || e.n > n0)) n0 = e.n;
-    if (e.n >= N && (n1 < 0 || e.n < n1)) n1 = e.n;
+  for (const int bc : {dash::kv_tile_rows(sched, d, causal, N, heads), 0}) {
+    const StepKey key{d, causal, sched, bc};
+    double n0 = -1, n1 = -1;  // nearest calibrated lengths at or below / at or above N
+    for (const dash::StepCost& e : dash::kStepCosts) {
+      if (e.n <= 0 || !key.takes(e)) continue;
+      if (e.n <= N && (n0 < 0 || e.n > n0)) n0 = e.n;
+      if (e.n >= N && (n1 < 0 || e.n < n1)) n1 = e.n;
+    }
+    if (n0 < 0 && n1 < 0) continue;
+    if (n0 < 0) return step_us_at(key, (int)n1, heads);
+    if (n1 < 0 || n1 == n0) return step_us_at(key, (int)n0, heads);
+    const double u0 = step_us_at(key, (int)n0, heads), u1 = step_us_at(key, (int)n1, heads);
+    const double f = std::log2((double)N / n0) / std::log2(n1 / n0);
+    return u0 + f * (u1 - u0);
   }
-  if (n0 < 0 && n1 < 0) return -1.0;
-  if (n0 < 0) return step_us_at(d, causal, sched, (int)n1, heads);
-  if (n1 < 0 || n1 == n0) return step_us_at(d, causal, sched, (int)n0, heads);
-  const double u0 = step_us_at(d, causal, sched, (int)n0, heads), u1 = step_us_at(d, causal, sched, (int)n1, heads);
-  const double f = std::log2((double)N / n0) / std::log2(n1 / n0);
-  return u0 + f * (u1 - u0);
+  return -1.0;
 }
 
 // Makespan of B*H heads on `workers` workgroups with compute c and reduction

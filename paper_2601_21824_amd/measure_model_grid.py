@@ -1,13 +1,12 @@
 """Measure the ordered schedules over a grid of shapes on the GPU: the data
 behind the block-step times of the DAG model that picks DASH_SCHED_AUTO.
 
-For d in (64, 128, 256), both masks, N from 512 to 16384 (d = 256: 4096 to
-32768) and B*H of 1, 2, 4, 16, 32, 64, 128, 256, 512 and 1024 heads (at most
-2^21 tokens and 6e13 FLOPs per call), every
-candidate deterministic schedule is timed as bench.py times a backward call
-(whole call, wall clock over back-to-back calls after 3 checked warm-up
-calls, >= 20 ms of work per timing), twice in opposite orders; the better of
-the two is kept.  One JSON line per shape on stdout, in the format of
+For d in (64, 128, 256), both masks, N from 512 (d = 128 and 256: from 64) to 16384
+(d = 256: 32768) and B*H from 1 to 1024 heads (at most 2^21 tokens and
+6e13 FLOPs per call), every candidate deterministic schedule is timed over
+back-to-back calls between two events, after 3 checked warm-up calls, at least
+10 ms of work per timing and up to 400 calls, four times in alternating order; the
+best is kept.  One JSON line per shape on stdout, in the format of
 ``bench.py --sweep``:
 
     python -m paper_2601_21824_amd.measure_model_grid > paper_2601_21824_amd/model_grid.jsonl
@@ -18,33 +17,28 @@ the two is kept.  One JSON line per shape on stdout, in the format of
 from __future__ import annotations
 
 import json
-import os
 import sys
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-
-
-HEADS = (1, 2, 4, 16, 32, 64, 128, 256, 512, 1024)
+HEADS = (1, 2, 4, 5, 8, 10, 16, 20, 32, 40, 64, 80, 128, 160, 256, 320, 512, 640, 1024)
 
 
 def shapes(dims=(64, 128, 256), heads=HEADS, masks=(False, True)):
     for d in dims:
-        lengths = (4096, 8192, 16384, 32768) if d == 256 else (512, 1024, 2048, 4096, 8192, 16384)
+        lengths = (64, 128, 256, 512, 1024, 2048, 4096, 8192, 16384, 32768)[3 if d == 64 else 0:10 if d == 256 else 9]
         for causal in masks:
-            for n in lengths:
-                for bh in heads:
-                    flops = 4.0 * bh * n * n * d * 2.5 / (2 if causal else 1)
-                    if bh * n <= (1 << 21) and flops <= 6e13:
-                        yield d, causal, n, bh
+            grid = [(n, bh) for n in lengths for bh in heads]
+            if d == 128 and not causal:  # one round of narrow tiles and a few more, which the grid passes over
+                grid += [(n, 36864 // n) for n in (384, 768, 1536, 3072, 6144, 12288)]
+            for n, bh in grid:
+                flops = 4.0 * bh * n * n * d * 2.5 / (2 if causal else 1)
+                if bh * n <= (1 << 21) and flops <= 6e13:
+                    yield d, causal, n, bh
 
 
 def main(*dims):
-    sys.path.insert(0, ROOT)
     import torch
 
-    import bench
     from paper_2601_21824_amd import binding as dash
-    from paper_2601_21824_amd.synth import make_inputs
 
     heads = HEADS
     if "--heads" in dims:
@@ -56,26 +50,37 @@ def main(*dims):
         i = dims.index("--mask")
         masks = (dims[i + 1] == "causal",)
         dims = dims[:i] + dims[i + 2:]
-    ev = bench.HipEvents()
+    begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     for d, causal, N, bh in shapes(tuple(int(x) for x in dims) or (64, 128, 256), heads, masks):
-        q, k, v, do = make_inputs(1, bh, N, d, seed=N + d + bh, sigma=0.5 if d == 256 else 1.0)
-        qg, kg, vg, dog = (t.cuda() for t in (q, k, v, do))
-        og, lseg = dash.attn_fwd(qg, kg, vg, causal)
-        dq, dk, dv = torch.empty_like(qg), torch.empty_like(kg), torch.empty_like(vg)
+        g = torch.Generator(device="cuda")
+        g.manual_seed(N + d + bh)
+        q, k, v, do = (torch.randn((1, bh, N, d), generator=g, device="cuda", dtype=torch.bfloat16) * (0.5 if d == 256 else 1.0)
+                       for _ in range(4))
+        o, lse = dash.attn_fwd(q, k, v, causal)
+        dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
         ws = dash.new_workspace(1, bh, N, d, "shift")
-        tensors = (qg, kg, vg, og, dog, lseg, dq, dk, dv, ws)
-        flops = 4.0 * bh * N * N * d * 2.5 / (2 if causal else 1)
+
+        def ms(sched, calls):
+            begin.record()
+            for _ in range(calls):
+                dash.dash_attn_bwd(q, k, v, o, do, lse, dq, dk, dv, causal, sched, workspace=ws)
+            end.record()
+            end.synchronize()
+            if dash.dash_bwd_check(ws) != dash.DASH_OK:
+                raise RuntimeError(f"{sched}: ordering wait timed out")
+            return begin.elapsed_time(end) / calls
+
         scheds = ["descending", "symshift", "naive"] if causal else ["shift", "descending", "naive"]
-        steps = max(5, min(200, int(20e-3 / (flops / 4e14))))
+        calls = {s: max(2, min(400, int(10.0 / min(ms(s, 1) for _ in range(3))))) for s in scheds}
         best = {}
-        for order in (scheds, scheds[::-1]):
+        for order in (scheds, scheds[::-1]) * 2:
             for s in order:
-                ms, _ = bench.time_schedule(dash, tensors, causal, s, steps, 3, ev)
-                best[s] = max(best.get(s, 0.0), flops / (ms * 1e-3) / 1e12)
+                best[s] = min(best.get(s, 1e30), ms(s, calls[s]))
+        flops = 4.0 * bh * N * N * d * 2.5 / (2 if causal else 1)
         row = {"B": 1, "H": bh, "N": N, "d": d, "mask": "causal" if causal else "full"}
-        row.update({s: round(best[s], 1) for s in scheds})
+        row.update({s: float(f"{flops / (best[s] * 1e-3) / 1e12:.4g}") for s in scheds})
         print(json.dumps(row), flush=True)
-        del tensors, qg, kg, vg, dog, og, lseg, dq, dk, dv, ws
+        del q, k, v, do, o, lse, dq, dk, dv, ws
         torch.cuda.empty_cache()
     return 0
 

@@ -174,3 +174,22 @@ def test_auto_cache_starts_over_with_the_same_answers():
     for n in range(1, 4200):
         b.dash_auto_schedule(1, 1, n, 64, n % 2 == 1, 256)
     assert [b.dash_auto_schedule(*s, 256) for s in shapes] == first
+
+
+def test_step_time_between_grid_shapes_is_that_of_the_calls_tile():
+    """A predicted time rests on the step time of shapes with the call's own KV
+    tile: at d = 128 from N = 2048 on, steps of 128-row tiles were measured at 3.1 to 4.8 us
+    and of 256-row tiles at 5.1 to 7.5, and no call lies in between."""
+    import random
+    rng = random.Random(4)
+    seen = set()
+    for _ in range(150):
+        causal = rng.random() < 0.5
+        n, heads = int(2048 * 8 ** rng.random()), int(64 ** rng.random())
+        sched, ms = b.dash_auto_schedule(1, heads, n, 128, causal, 256)
+        tab = b.dash_schedule_table(sched, n, 128, causal, heads=heads)
+        unit = b.dash_model_makespan(sched, 1, heads, n, 128, causal, 256, 0.02, 0.98, max_heads=-(-3 * 256 // tab["chains"]))
+        step = ms * 1e3 / unit
+        assert (3.0 < step < 4.85) if tab["bc"] == 128 else (5.0 < step < 7.6), (sched, heads, n, causal, step)
+        seen.add((causal, tab["bc"]))
+    assert len(seen) == 4
