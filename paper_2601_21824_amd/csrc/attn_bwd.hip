@@ -24,11 +24,12 @@ namespace dash {
 // Memory-bound: O and dO are read once.  A wave takes U times 64 / TPR rows in
 // a row, all their loads issued before the first is used, and writes their D
 // and L with one store each.  O, which nothing reads again, is loaded past the
-// caches that dO stays in for the main kernel.
+// caches that dO stays in for the main kernel (not beside the atomic variant's
+// zeroing of its accumulator: 15.1 us there, 17.6 with it, 919 heads of 192 at d = 64).
 // Measured (us, one row per thread -> four): 16 MB of O and dO each 8.1 -> 7.1,
 // 67 MB 27.4 -> 22.9 (5.9 TB/s), 134 MB 55.4 -> 53.3.
-template <int D, int U>
-__global__ __launch_bounds__(256) void bwd_pre_kernel(BwdArgs a, int zero_acc) {
+template <int D, int U, bool ZERO>
+__global__ __launch_bounds__(256) void bwd_pre_kernel(BwdArgs a) {
   constexpr int TPR = D / 8;    // threads per row, 8 elements each
   constexpr int RPL = 64 / TPR;  // rows of a wave's load instruction
   static_assert(U <= TPR, "lane c of a row writes row c of its U");
@@ -44,7 +45,8 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(BwdArgs a, int zero_acc) {
       long row = row0 + u * RPL + l / TPR;
       row = row < rows ? row : rows - 1;  // (read, not written)
       x[u] = *(const u32x4*)((const __bf16*)a.dO + row * D + 8 * c);
-      y[u] = __builtin_nontemporal_load((const u32x4*)((const __bf16*)a.o + row * D + 8 * c));
+      const u32x4* o = (const u32x4*)((const __bf16*)a.o + row * D + 8 * c);
+      y[u] = ZERO ? *o : __builtin_nontemporal_load(o);
     }
     float mine = 0.f;
 #pragma unroll
@@ -123,7 +125,7 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(BwdArgs a, int zero_acc) {
       }
     }
   }
-  if (zero_acc) {
+  if (ZERO) {
     const long n4 = (long)a.bh * a.n * D / 4;
     for (long i = gtid; i < n4; i += (long)nthreads) ((f32x4*)a.dqacc)[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
@@ -183,12 +185,12 @@ hipError_t launch_all(const BwdArgs& a, int grid_main, hipStream_t stream) {
   // -> 7.2 us there, 27 -> 23 at 16384); at 2048 both take 5.0 and below that
   // (1024: 4.2-4.6 against 4.3-4.8) more waves are worth more
   const long one = ((long)a.bh * a.n * (D / 8) + 255) / 256;  // workgroups of one row per thread group
-  if (one >= 4096) {
-    const long blocks = (one + 3) / 4;
-    hipLaunchKernelGGL((bwd_pre_kernel<D, 4>), dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0, stream, a, (int)atomic);
-  } else {
-    hipLaunchKernelGGL((bwd_pre_kernel<D, 1>), dim3((unsigned)one), dim3(256), 0, stream, a, (int)atomic);
-  }
+  const long four = (one + 3) / 4;
+  const dim3 grid((unsigned)(one < 4096 ? one : four < 65536 ? four : 65536));
+  if (one < 4096)
+    hipLaunchKernelGGL((atomic ? bwd_pre_kernel<D, 1, true> : bwd_pre_kernel<D, 1, false>), grid, dim3(256), 0, stream, a);
+  else
+    hipLaunchKernelGGL((atomic ? bwd_pre_kernel<D, 4, true> : bwd_pre_kernel<D, 4, false>), grid, dim3(256), 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (a.ev_begin) (void)hipEventRecord(a.ev_begin, stream);

@@ -259,7 +259,9 @@ __global__ __launch_bounds__(256) void bwd_main64w_kernel(BwdArgs a) {
       // 64 heads of 8192 full 3971 -> 3920 us, causal 2244 -> 2192; forward and
       // backward of 128 heads of 2100 causal 478.7 -> 469.9.  Keeping dK and dV in
       // AGPRs by asm besides, as bwd_mainw_kernel does, takes the register moves
-      // out of the step but measured 1-3% slower.
+      // out of the step but measured 1-3% slower.  (Not in the atomic variant, which
+      // the reads ahead cost 1.6% of its time: each of its runs reads its own first.)
+      constexpr bool kCross = MODE != kModeAtomic;
       bf16x8 fq[4], fo[4];
       static_assert(KS == 4 && 2 * NB == 4, "four slots per run");
       // S = Q K^T, dP = dO V^T of query half qb and key block kb: A = Q / dO
@@ -271,6 +273,9 @@ __global__ __launch_bounds__(256) void bwd_main64w_kernel(BwdArgs a) {
       };
       f32x16 s[2], dp[2];
       auto sdp = [&](int qb, int kb, auto&& next, auto&& extra) {
+        if constexpr (!kCross)
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) rd_rows(qb, ks);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           s[qb][r] = 0.f;
@@ -281,7 +286,7 @@ __global__ __launch_bounds__(256) void bwd_main64w_kernel(BwdArgs a) {
           __builtin_amdgcn_sched_barrier(0);
           s[qb] = mfma32(fq[ks], kreg[kb][ks], s[qb]);
           dp[qb] = mfma32(fo[ks], vreg[kb][ks], dp[qb]);
-          next(ks);
+          if constexpr (kCross) next(ks);
           extra(ks);
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -351,13 +356,16 @@ __global__ __launch_bounds__(256) void bwd_main64w_kernel(BwdArgs a) {
       };
       auto dvdk = [&](int qb, int kb, auto&& next, auto&& extra) {
         constexpr int NP = 2 * NB;
+        if constexpr (!kCross)
+#pragma unroll
+          for (int k = 0; k < NP; ++k) rd_cols(qb, k);
 #pragma unroll
         for (int k = 0; k < NP; ++k) {
           __builtin_amdgcn_sched_barrier(0);
           const int nb = k >> 1, half = k & 1;
           dvacc[kb][nb] = mfma32(pbf[qb][half], fo[k], dvacc[kb][nb]);
           dkacc[kb][nb] = mfma32(dsbf[qb][half], fq[k], dkacc[kb][nb]);
-          next(k);
+          if constexpr (kCross) next(k);
           extra(k);
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -379,8 +387,9 @@ __global__ __launch_bounds__(256) void bwd_main64w_kernel(BwdArgs a) {
       };
 
       bool early_acc = false;
+      if constexpr (kCross)
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) rd_rows(0, ks);
+        for (int ks = 0; ks < KS; ++ks) rd_rows(0, ks);
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb) {
         // run 1: S/dP of half 0 (key block 0: with the next block's Q / dO /
@@ -457,7 +466,10 @@ __global__ __launch_bounds__(256) void bwd_main64w_kernel(BwdArgs a) {
         {
           constexpr int RING = 4;
 #pragma unroll
-          for (int k = 0; k < RING; ++k) fo[k] = rd_ds(k);
+          for (int k = 0; k < RING; ++k) {
+            if constexpr (!kCross) fq[k] = rd_kt(k);
+            fo[k] = rd_ds(k);
+          }
 #pragma unroll
           for (int ks = 0; ks < KSC; ++ks) {
             __builtin_amdgcn_sched_barrier(0);
