@@ -139,7 +139,6 @@ __global__ __launch_bounds__(NT) void bwd_mainw_kernel(BwdArgs a) {
     const auto rq = make_rsrc((const __bf16*)a.q + head, hbytes);
     const auto rk = make_rsrc((const __bf16*)a.k + head, hbytes);
     const auto rdo = make_rsrc((const __bf16*)a.dO + head, hbytes);
-    const auto racc = make_rsrc(a.dqacc + (size_t)bh * a.nblk * BM * D, (uint32_t)a.nblk * BM * D * 4);
     int* ctr_head = a.counters + (size_t)bh * a.nblk * kCtrStride;
     const auto rctr = make_rsrc(ctr_head, (uint32_t)a.nblk * kCtrStride * 4);
 

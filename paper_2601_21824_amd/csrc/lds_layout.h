@@ -1,4 +1,4 @@
-// lds_layout.h -- where the backward kernels keep bf16 tiles in LDS.
+// lds_layout.h -- where the kernels keep bf16 tiles in LDS.
 //
 // The LDS of gfx950 has 64 banks of 4 bytes.  A read of 16 bytes per lane is
 // served 16 lanes at a time (lanes 0-15, 16-31, 32-47, 48-63); a read or write
@@ -8,7 +8,7 @@
 // counter on a one-wave probe of fixed address patterns.)
 //
 // Each swizzle below puts the lanes of every group of every access the
-// kernels make on distinct banks; a host test checks them against this model
+// kernels make to these tiles in their steps on distinct banks; a host test checks them against this model
 // with the kernels' lane mappings.  Functions are usable on host and device.
 #pragma once
 

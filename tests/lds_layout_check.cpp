@@ -1,5 +1,7 @@
-// Bank-conflict check of the backward kernels' LDS layouts (host build of
-// paper_2601_21824_amd/csrc/lds_layout.h).
+// Bank-conflict check of the kernels' LDS layouts (host build of
+// paper_2601_21824_amd/csrc/lds_layout.h), and of the address arithmetic by
+// which the wide-tile backward and the forward reach them (a lane's base address
+// with the step entered by XOR or as an offset).
 //
 // Bank model of gfx950 (measured with the hardware bank-conflict counter on a
 // one-wave probe): 64 banks of 4 bytes; 16-byte-per-lane accesses are served
@@ -164,6 +166,138 @@ static void d256_patterns() {
   expect("d=256 dS^T transposed reads (per wave and step)", rd, 0);
 }
 
+static void same(const char* what, long got, long want) {
+  if (got == want) return;
+  std::printf("%s: address %ld, expected %ld\n", what, got, want);
+  ++failures;
+}
+
+// Direct global -> LDS copies of a [rows][D] tile: thread t of 256 writes 16 bytes
+// at 16 t (+ 4096 per part) and reads chunk (t % (D/8)) ^ swz(row) of its row.
+template <int D>
+static void copy_lands(int rows) {
+  const int CPR = D / 8;
+  for (int p = 0; p < rows * CPR / 256; ++p)
+    for (int t = 0; t < 256; ++t) {
+      const int row = t / CPR + p * (256 / CPR), c = (t % CPR) ^ tile_swz<D>(row);
+      same("direct copy", 16L * t + 4096L * p, 2L * bf_at<D>(row, 8 * c));
+    }
+}
+
+// bwd_mainw_kernel (attn_bwdw.hip): KV tile of BC = 32768 / D rows, sub-steps of
+// 32 queries
+template <int D>
+static void wide_patterns(const char* name) {
+  const int BC = 32768 / D, NKB = BC / 128, NB = D / 32, KS = D / 16;
+  int rows = 0, krows = 0, tr = 0, wr = 0, rdk = 0, rdd = 0;
+  for (int ks = 0; ks < KS; ++ks) {
+    std::vector<long> a(64);
+    for (int l = 0; l < 64; ++l) {  // phase 1: Q / dO rows
+      a[l] = (2L * bf_at<D>(l & 31, 8 * (l >> 5))) ^ (ks << 5);
+      same("wide Q row", a[l], 2L * bf_at<D>(l & 31, 16 * ks + 8 * (l >> 5)));
+    }
+    rows += conflicts(a, 16);
+    for (int w = 0; w < 4; ++w)  // K rows of the wave's key blocks
+      for (int kb = 0; kb < NKB; ++kb) {
+        for (int l = 0; l < 64; ++l) {
+          a[l] = ((2L * bf_at<D>(32 * NKB * w + (l & 31), 8 * (l >> 5))) ^ (ks << 5)) + 32L * kb * D * 2;
+          same("wide K row", a[l], 2L * bf_at<D>(32 * (NKB * w + kb) + (l & 31), 16 * ks + 8 * (l >> 5)));
+        }
+        krows += conflicts(a, 16);
+      }
+  }
+  for (int i = 0; i < 2 * NB; ++i)  // phase 3: transposed Q / dO
+    for (int e = 0; e < 2; ++e) {
+      std::vector<long> a(64);
+      for (int l = 0; l < 64; ++l) {
+        const int L16 = l & 15, nh = (l >> 4) & 1, g = l >> 5, row = 4 * g + (L16 >> 2) + 8 * e, col = 16 * nh + 4 * (L16 & 3);
+        a[l] = ((2L * bf_at<D>(row, col)) ^ ((i >> 1) << 6)) + 16L * (i & 1) * D * 2;
+        same("wide Q column", a[l], 2L * bf_at<D>(row + 16 * (i & 1), col + 32 * (i >> 1)));
+      }
+      tr += conflicts(a, 8);
+    }
+  for (int kb = 0; kb < BC / 32; ++kb)  // phase 3: dS^T stores of 32 keys
+    for (int rb = 0; rb < 4; ++rb) {
+      std::vector<long> a(64);
+      for (int l = 0; l < 64; ++l) a[l] = 2L * dst32_at(32 * kb + (l & 31), 8 * rb + 4 * (l >> 5));
+      wr += conflicts(a, 8);
+    }
+  for (int ks = 0; ks < BC / 16; ++ks)  // phase 2: dQ^T
+    for (int e = 0; e < 2; ++e) {
+      std::vector<long> a(64);
+      for (int db = 0; db < NB; ++db) {
+        for (int l = 0; l < 64; ++l) {
+          const int L16 = l & 15, nh = (l >> 4) & 1, g = l >> 5, row = 8 * g + (L16 >> 2) + 4 * e, col = 16 * nh + 4 * (L16 & 3);
+          a[l] = 2L * bf_at<D>(row, 32 * db + col) + 16L * ks * D * 2;
+          same("wide K column", a[l], 2L * bf_at<D>(row + 16 * ks, 32 * db + col));
+        }
+        rdk += conflicts(a, 8);
+      }
+      for (int l = 0; l < 64; ++l) {
+        const int L16 = l & 15, nh = (l >> 4) & 1, g = l >> 5, row = 8 * g + (L16 >> 2) + 4 * e, col = 16 * nh + 4 * (L16 & 3);
+        a[l] = ((2L * dst32_at(row, col)) ^ (32 * (ks & 1))) + 16L * ks * 32 * 2;
+        same("wide dS^T", a[l], 2L * dst32_at(row + 16 * ks, col));
+      }
+      rdd += conflicts(a, 8);
+    }
+  std::set<long> cells;  // dst32_at keeps 4 queries together and every slot apart
+  for (int r = 0; r < BC; ++r)
+    for (int q = 0; q < 32; q += 4) cells.insert(dst32_at(r, q));
+  same("dst32_at cells", (long)cells.size(), 8L * BC);
+  same("dst32_at last cell", *cells.rbegin(), 32L * BC - 4);
+  copy_lands<D>(32);
+  copy_lands<D>(BC);
+  char buf[96];
+  std::snprintf(buf, sizeof buf, "%s wide Q/dO row operands (per sub-step)", name);
+  expect(buf, rows, 0);
+  std::snprintf(buf, sizeof buf, "%s wide K row operands (all waves)", name);
+  expect(buf, krows, 0);
+  std::snprintf(buf, sizeof buf, "%s wide Q/dO transposed operands", name);
+  expect(buf, tr, 0);
+  std::snprintf(buf, sizeof buf, "%s wide dS^T stores (all waves)", name);
+  expect(buf, wr, 0);
+  std::snprintf(buf, sizeof buf, "%s wide K^T transposed reads (all d blocks)", name);
+  expect(buf, rdk, 0);
+  std::snprintf(buf, sizeof buf, "%s wide dS^T transposed reads", name);
+  expect(buf, rdd, 0);
+}
+
+// attn_fwd_kernel: K and V tiles of KT rows, in units of 32 keys
+template <int D>
+static void fwd_patterns(const char* name) {
+  const int KT = D == 256 ? 32 : 64;
+  int k = 0, v = 0;
+  for (int uu = 0; uu < KT / 32; ++uu) {
+    for (int ks = 0; ks < D / 16; ++ks) {
+      std::vector<long> a(64);
+      for (int l = 0; l < 64; ++l) {
+        const int g = l >> 5, lc = l & 31;
+        a[l] = ((lc * D * 2 + ((g ^ tile_swz<D>(lc)) << 4)) ^ (ks << 5)) + 32L * uu * D * 2;
+        same("forward K row", a[l], 2L * bf_at<D>(32 * uu + lc, 16 * ks + 8 * g));
+      }
+      k += conflicts(a, 16);
+    }
+    for (int p = 0; p < D / 16; ++p)
+      for (int e = 0; e < 2; ++e) {
+        std::vector<long> a(64);
+        const int half = p / (D / 32), db = p % (D / 32);
+        for (int l = 0; l < 64; ++l) {
+          const int L16 = l & 15, nh = (l >> 4) & 1, g = l >> 5, row = 4 * g + (L16 >> 2) + 8 * e;
+          const long lane = row * D * 2 + (((2 * nh + ((L16 & 3) >> 1)) ^ tile_swz<D>(row)) << 4) + ((L16 & 1) << 3);
+          a[l] = (lane ^ (db << 6)) + (32L * uu + 16 * half) * D * 2;
+          same("forward V column", a[l], 2L * bf_at<D>(32 * uu + 16 * half + row, 32 * db + 16 * nh + 4 * (L16 & 3)));
+        }
+        v += conflicts(a, 8);
+      }
+  }
+  copy_lands<D>(KT);
+  char buf[96];
+  std::snprintf(buf, sizeof buf, "%s forward K row operands (per tile)", name);
+  expect(buf, k, 0);
+  std::snprintf(buf, sizeof buf, "%s forward V^T transposed operands (per tile)", name);
+  expect(buf, v, 0);
+}
+
 static void probe_patterns() {
   // the probe's measured conflict cycles per instruction
   auto rows_at = [](int period) {
@@ -193,6 +327,11 @@ int main() {
   dst_patterns();
   w64_patterns();
   d256_patterns();
+  wide_patterns<128>("d=128");
+  wide_patterns<256>("d=256");
+  fwd_patterns<64>("d=64");
+  fwd_patterns<128>("d=128");
+  fwd_patterns<256>("d=256");
   std::printf(failures ? "FAIL\n" : "OK\n");
   return failures ? 1 : 0;
 }

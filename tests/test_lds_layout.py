@@ -1,5 +1,5 @@
-"""Host check of the backward kernels' LDS layouts: every access pattern of
-the d = 64 / 128 / 256 kernels is bank-conflict free under gfx950's measured
+"""Host check of the kernels' LDS layouts: every access pattern of the backward
+and forward kernels' tiles at d = 64 / 128 / 256 is bank-conflict free under gfx950's measured
 bank model (64 banks of 4 bytes; 16-byte accesses served 16 lanes at a time,
 8-byte accesses 32 at a time).  The model itself is pinned by the conflict
 counts a one-wave hardware probe measured for fixed address patterns."""
