@@ -121,14 +121,17 @@ def ordering_wait(dash, tensors, causal, sched, B, H, N, d):
             "late_frac": round(late / wave_steps, 4) if wave_steps else None}
 
 
+# counters of the kernel that runs the default workload
+TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "bwd_mainw_b2h16n8192d128_full.md")
+
+
 def measured_traffic():
     """HBM bytes per launch of the main kernel from the committed rocprofv3
     FETCH_SIZE / WRITE_SIZE summary, or None if the kernel source changed since
     the counters were taken."""
     import hashlib
-    summary = os.path.join(ROOT, "profiles", "bwd_mainw_b2h16n8192d128_full.md")
     try:
-        text = open(summary).read()
+        text = open(TRAFFIC_SUMMARY).read()
         fields = dict(line.split(": ", 1) for line in text.splitlines() if ": " in line and not line.startswith(" "))
         src = os.path.join(ROOT, fields["source_file"].strip())
         sha = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
@@ -137,6 +140,20 @@ def measured_traffic():
     if fields.get("source_sha256_prefix", "").strip() != sha:
         return None
     return float(fields["traffic_bytes_per_launch"])
+
+
+def time_forward(dash, tensors, causal, steps, warmup):
+    """Mean ms per forward call over `steps` back-to-back calls."""
+    import torch
+    q, k, v, o, _, lse = tensors[:6]
+    for _ in range(warmup):
+        dash.dash_attn_fwd(q, k, v, o, lse, causal)
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    for _ in range(steps):
+        dash.dash_attn_fwd(q, k, v, o, lse, causal)
+    torch.cuda.synchronize()
+    return (time.perf_counter() - t0) * 1e3 / steps
 
 
 def cpu_baseline(q, k, v, do, causal, flops_per_head):
@@ -223,6 +240,7 @@ def main():
                          "d=64: H=32, both masks), the B=4 H=16 N=1024 d=64 causal case and B=1 H=8 "
                          "N=32768 d=256 (both masks), twice in opposite orders (the faster kept); "
                          "one JSON line per case")
+    ap.add_argument("--forward", action="store_true", help="only time the forward of the workload")
     ap.add_argument("--copy-bytes", type=int, default=0,
                     help="only run 5 plain device copies of this many bytes (counter calibration)")
     args = ap.parse_args()
@@ -266,6 +284,12 @@ def main():
     tensors = (qg, kg, vg, og, dog, lseg, dq, dk, dv, ws)
     ev = HipEvents()
 
+    if args.forward:
+        ms = time_forward(dash, tensors, causal, args.steps, args.warmup)
+        print(json.dumps({"forward": f"B={B} H={H} N={N} d={d} {'causal' if causal else 'full'} mask", "ms": ms,
+                          "tflops": flops / 2.5 / (ms * 1e-3) / 1e12}), flush=True)
+        return
+
     results = {}
     per_call = {}
     spin_calls = spin_up(dash, tensors, causal, scheds[0], args.spinup_ms)
@@ -307,6 +331,8 @@ def main():
                    "B": B, "H": H, "N": N, "d": d, "mask": "causal" if causal else "full",
                    "schedule": det, "global_batch": B, "seq_len": N},
         "pct_of_atomic": round(100.0 * tflops / results["atomic"][2], 2),
+        # the two sides' KV tiles: the atomic variant has the narrow one only at d = 128 and 256
+        "kv_tile_rows": {det: bc, "atomic": dash.dash_schedule_table("atomic", N, d, causal, heads=B * H)["bc"]},
         "atomic_tflops": round(results["atomic"][2], 2),
         "naive_tflops": round(results["naive"][2], 2) if "naive" in results else None,
         "roofline": {"bound": "mfma", "kernel": f"{kname}<{d}, "

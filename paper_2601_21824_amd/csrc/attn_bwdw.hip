@@ -23,12 +23,14 @@
 // parity, which is its half h of the block).  The accumulator slice goes to
 // registers directly, as the block's 32 queries leave room for it.
 //
-// What bounds it: a wave issues one VALU instruction per 5.4 cycles when it is
-// alone on its SIMD (4 when two share it), so a sub-step's 500 VALU and 150 LDS
-// instructions take about as long as its 80 MFMAs, and the LDS reads of phase 1
-// (128 KB per CU) longer than its MFMAs; the accumulator's 1 KB device-coherent
+// What bounds it: the issue of one wave per SIMD.  Of the about 6,000 cycles of a
+// sub-step (d = 128, full) the matrix cores are busy 2,560; the wave's 460 VALU
+// instructions, its 80 MFMAs among them, are active for about 2,000, its LDS instructions
+// for 650, and it waits for about 1,300 (counters and clock by rocprofv3, in
+// profiles/bwd_mainw_b2h16n8192d128_full.md).  The LDS reads of phase 1 (128 KB
+// per CU) take longer than its MFMAs, and the accumulator's 1 KB device-coherent
 // loads and stores cost a wave 100-300 cycles each where they stand close together,
-// hence one per 2-4 MFMAs.  Of 6,430 cycles per sub-step 2,560 are MFMA.
+// hence one per 2-4 MFMAs.
 //
 // Measured (main kernel and bwd_pre, us, narrow tile -> this): d = 128, 32 heads of
 // 8192 full 3901 -> 3176 (705 -> 866 TFLOP/s), 64 heads causal 4199 -> 3360; d =

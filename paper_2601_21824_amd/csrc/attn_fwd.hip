@@ -13,19 +13,20 @@
 // What bounds it: matrix instructions (4 N^2 d FLOP) and, next to them, the
 // softmax's VALU work (fused multiply-add, exp, sum, half a max and half a
 // conversion per score), which a wave can only overlap with its own MFMAs where
-// it stands between two of them (measured: one MFMA hides 6 VALU instructions of
-// its wave).  So the loop is software-pipelined: while unit u's scores go through
+// it stands between two of them (one MFMA hid 6 VALU instructions of its wave in
+// a probe).  So the loop is software-pipelined: while unit u's scores go through
 // exp, the matrix cores compute unit u+1's scores; while O^T of unit u is summed,
 // the VALU adds unit u's row sum and takes unit u+1's maximum; and every MFMA
 // is followed by its share of that work.  Two waves per SIMD fill each other's
-// waits.  Long calls run at the power limit: N = 8192, d = 128 keeps the matrix
-// cores busy for 57% of 1.75 GHz.
+// waits.  Long calls run at the power limit (profiles/attn_fwd.md has the clock and
+// the matrix cores' share of it).
 //
-// Measured (us, before -> now; before: 64-key steps staged through registers,
-// no overlap of scores, softmax and O): 64 heads of 8192 at d = 128, causal
-// 2400 -> 1175 (459 -> 937 TFLOP/s); 32 heads full 1640 -> 1105; 64 heads of
-// 8192 at d = 64 full 1990 -> 1225, causal 1490 -> 708; 8 heads of 16384 at
-// d = 256 full 4640 -> 2276; 1024 heads of 512 at d = 128 causal 264 -> 163.
+// Measured (us, in turn on one card, before -> now; before: 64-key steps staged
+// through registers, no overlap of scores, softmax and O): 64 heads of 8192 at d = 128
+// causal 2494 -> 1183 (441 -> 929 TFLOP/s); 32 heads full 1639 -> 1077; 64 heads
+// of 8192 at d = 64 full 1991 -> 1208, causal 1492 -> 697; 8 heads of 16384 at
+// d = 256 full 4625 -> 2254; 1024 heads of 512 at d = 128 causal 263 -> 163.  Cards
+// differ by 5%.
 #include <type_traits>
 
 #include "common.h"

@@ -37,3 +37,16 @@ def test_sources_named_exist():
         assert srcs, path
         for src, _ in srcs:
             assert os.path.isfile(os.path.join(ROOT, src)), (path, src)
+
+
+def test_bench_names_a_summary_of_the_kernel_it_runs():
+    """The traffic of bench.py's roofline comes from a committed summary of the
+    kernel that the default workload (B=2 H=16 N=8192 d=128 full, Shift) runs."""
+    import bench
+    from paper_2601_21824_amd import binding as b
+    bc = b.dash_schedule_table("shift", 8192, 128, False, heads=32)["bc"]
+    text = open(bench.TRAFFIC_SUMMARY).read()
+    assert text.startswith("# bwd_mainw_kernel<128" if bc == 256 else "# bwd_main_kernel<128")
+    fields = dict(l.split(": ", 1) for l in text.splitlines() if ": " in l and not l.startswith(" "))
+    assert os.path.isfile(os.path.join(ROOT, fields["source_file"]))
+    assert float(fields["traffic_bytes_per_launch"]) > 0
