@@ -26,8 +26,8 @@
 // What bounds it: the issue of one wave per SIMD.  Of the about 6,000 cycles of a
 // sub-step (d = 128, full) the matrix cores are busy 2,560; the wave's 460 VALU
 // instructions, its 80 MFMAs among them, are active for about 2,000, its LDS instructions
-// for 650, and it waits for about 1,300 (counters and clock by rocprofv3, in
-// profiles/bwd_mainw_b2h16n8192d128_full.md).  The LDS reads of phase 1 (128 KB
+// for 650, and it waits for about 1,300 (hardware counters over the benchmark's
+// launch, at 1.93 GHz).  The LDS reads of phase 1 (128 KB
 // per CU) take longer than its MFMAs, and the accumulator's 1 KB device-coherent
 // loads and stores cost a wave 100-300 cycles each where they stand close together,
 // hence one per 2-4 MFMAs.
