@@ -3,8 +3,10 @@
 // Host code only; the kernels live in attn_fwd.hip and attn_bwd.hip.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <iterator>
 #include <map>
 #include <mutex>
 #include <string>
@@ -286,18 +288,28 @@ bool auto_chain_major(int sched, int causal, int d, long chains, long resident, 
 // tile, so that a wide one is twice the work, and between a narrow and a wide
 // shape the time does not run along a line but steps where the tile changes (5 heads of
 // 8192 full at d = 128 would get 4.5 us for wide steps of 6.4).
-struct StepKey {
-  int d, causal, sched, bc;  // bc: rows per KV tile (0: any)
+struct StepCosts {  // the entries of (d, mask, schedule), which stand together, with KV tiles of bc rows (0: any)
+  int bc;
+  const dash::StepCost *first, *last;
+  StepCosts(int d, int causal, int sched) : bc(0) {
+    const auto key = std::make_tuple(d, causal, sched);
+    auto of = [](const dash::StepCost& e) { return std::make_tuple(e.d, e.causal, e.sched); };
+    first = std::lower_bound(std::begin(dash::kStepCosts), std::end(dash::kStepCosts), key,
+                             [&](const dash::StepCost& e, const auto& k) { return of(e) < k; });
+    last = std::upper_bound(first, std::end(dash::kStepCosts), key,
+                            [&](const auto& k, const dash::StepCost& e) { return k < of(e); });
+  }
+  const dash::StepCost* begin() const { return first; }
+  const dash::StepCost* end() const { return last; }
   bool takes(const dash::StepCost& e) const {
-    return e.d == d && e.causal == causal && e.sched == sched &&
-           (bc == 0 || dash::kv_tile_rows(sched, d, causal, e.n, e.heads) == bc);
+    return bc == 0 || dash::kv_tile_rows(e.sched, e.d, e.causal, e.n, e.heads) == bc;
   }
 };
 
-double step_us_at(const StepKey& key, int n, long heads) {
+double step_us_at(const StepCosts& costs, int n, long heads) {
   double h0 = -1, u0 = 0, h1 = -1, u1 = 0;  // nearest calibrated head counts below / above
-  for (const dash::StepCost& e : dash::kStepCosts) {
-    if (e.n != n || !key.takes(e)) continue;
+  for (const dash::StepCost& e : costs) {
+    if (e.n != n || !costs.takes(e)) continue;
     if (e.heads <= heads && (h0 < 0 || e.heads > h0)) h0 = e.heads, u0 = e.us;
     if (e.heads >= heads && (h1 < 0 || e.heads < h1)) h1 = e.heads, u1 = e.us;
   }
@@ -308,18 +320,19 @@ double step_us_at(const StepKey& key, int n, long heads) {
 }
 
 double step_us(int d, int causal, int sched, int N, long heads) {
+  StepCosts costs(d, causal, sched);
   for (const int bc : {dash::kv_tile_rows(sched, d, causal, N, heads), 0}) {
-    const StepKey key{d, causal, sched, bc};
+    costs.bc = bc;
     double n0 = -1, n1 = -1;  // nearest calibrated lengths at or below / at or above N
-    for (const dash::StepCost& e : dash::kStepCosts) {
-      if (e.n <= 0 || !key.takes(e)) continue;
+    for (const dash::StepCost& e : costs) {
+      if (e.n <= 0 || !costs.takes(e)) continue;
       if (e.n <= N && (n0 < 0 || e.n > n0)) n0 = e.n;
       if (e.n >= N && (n1 < 0 || e.n < n1)) n1 = e.n;
     }
     if (n0 < 0 && n1 < 0) continue;
-    if (n0 < 0) return step_us_at(key, (int)n1, heads);
-    if (n1 < 0 || n1 == n0) return step_us_at(key, (int)n0, heads);
-    const double u0 = step_us_at(key, (int)n0, heads), u1 = step_us_at(key, (int)n1, heads);
+    if (n0 < 0) return step_us_at(costs, (int)n1, heads);
+    if (n1 < 0 || n1 == n0) return step_us_at(costs, (int)n0, heads);
+    const double u0 = step_us_at(costs, (int)n0, heads), u1 = step_us_at(costs, (int)n1, heads);
     const double f = std::log2((double)N / n0) / std::log2(n1 / n0);
     return u0 + f * (u1 - u0);
   }
