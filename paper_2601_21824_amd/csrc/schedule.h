@@ -104,6 +104,9 @@ DASH_HD double tile_time(int sched, int causal, int N, long heads, int bc, doubl
 // and a last round that few wide tiles begin are slower with it: 264 heads of
 // 128 full at d = 128 35.5 us narrow, 52.0 wide; 9 of 8192 1299 and 1440; 264 of 128
 // causal at d = 256 55.2 and 81.9.
+// (Symmetric Shift at d = 128 beyond 64 narrow tiles is left out of that: its 32 and
+// fewer chains of wide tiles fit one XCD, which placement there asks for, and both
+// tiles take the same time where the rounds favour the narrow one: 18 heads of 9674.)
 // The atomic variant and SPLIT's dK, dV pass (no ordered accumulator) exist for
 // the narrow tile only at d = 128 and 256.  The tile size is part of the
 // summation order, so it is a function of the problem (schedule, d, mask, N,
@@ -116,7 +119,8 @@ DASH_HD int kv_tile_rows(int sched, int d, int causal, int N, long heads) {
   else if (sched == S_ATOMIC || sched == S_SPLIT) w = false;
   else if (d == 128) w = causal ? (N > 256 && wide >= 384) : wide >= 160;
   else w = heads > 1 && wide >= (causal ? 192 : 128);
-  if (w && (d == 128 || (d == 256 && N < 512))) {
+  const bool folds_on_xcd = d == 128 && sched == S_SYMSHIFT && N > 64 * narrow;
+  if (w && !folds_on_xcd && (d == 128 || (d == 256 && N < 512))) {
     const bool uneven = causal && sched != S_SYMSHIFT;
     const double step = uneven ? 1.45 : d == 128 ? 1.5 : 1.2, fill = d == 128 ? 0.5 : 0.25, start = d == 128 ? 1.0 : 0.0;
     w = tile_time(sched, causal, N, heads, narrow, 1.0, fill, 0.5 * start) >

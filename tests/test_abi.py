@@ -111,7 +111,7 @@ def tile_rows(sched, d, causal, N, heads):
         return bc
     if causal and N < {64: 1024, 128: 257, 256: 0}[d] or d == 256 and heads == 1:
         return bc
-    if d == 64 or d == 256 and N >= 512:
+    if d == 64 or d == 256 and N >= 512 or d == 128 and sched == b.DASH_SCHED_SYMSHIFT and N > 8192:
         return 2 * bc
 
     even = not causal or sched == b.DASH_SCHED_SYMSHIFT
@@ -155,7 +155,7 @@ FASTER = [("shift", 264, 64, 128, False, 128), ("shift", 264, 128, 128, False, 1
           ("descending", 264, 97, 256, True, 64),
           ("shift", 32, 8192, 128, False, 256), ("symshift", 64, 8192, 128, True, 256), ("descending", 64, 8192, 128, True, 256),
           ("shift", 256, 256, 128, False, 256), ("descending", 1024, 512, 128, True, 256), ("descending", 8, 32768, 256, True, 128),
-          ("symshift", 8, 32768, 256, True, 128), ("descending", 72, 387, 256, True, 128), ("shift", 33, 900, 256, False, 128), ("descending", 25, 1280, 256, True, 128)]
+          ("symshift", 8, 32768, 256, True, 128), ("symshift", 18, 9674, 128, True, 256), ("descending", 72, 387, 256, True, 128), ("shift", 33, 900, 256, False, 128), ("descending", 25, 1280, 256, True, 128)]
 
 
 @pytest.mark.parametrize("sched,heads,N,d,causal,rows", FASTER)
