@@ -2,7 +2,7 @@
 behind the block-step times of the DAG model that picks DASH_SCHED_AUTO.
 
 For d in (64, 128, 256), both masks, N from 512 (d = 128 and 256: from 64) to 16384
-(d = 256: 32768) and B*H from 1 to 1024 heads (at most 2^21 tokens and
+(d = 256: 32768) and B*H from 1 to 1024 heads (see shapes; at most 2^21 tokens and
 6e13 FLOPs per call), every candidate deterministic schedule is timed over
 back-to-back calls between two events, after 3 checked warm-up calls, at least
 10 ms of work per timing and up to 400 calls, four times in alternating order; the
@@ -24,10 +24,13 @@ HEADS = (1, 2, 4, 5, 8, 10, 16, 20, 32, 40, 64, 80, 128, 160, 256, 320, 512, 640
 
 def shapes(dims=(64, 128, 256), heads=HEADS, masks=(False, True)):
     for d in dims:
-        lengths = (64, 128, 256, 512, 1024, 2048, 4096, 8192, 16384, 32768)[3 if d == 64 else 0:10 if d == 256 else 9]
+        # (192 to 768: there most calls change their tile, which cuts a line between two lengths short)
+        lengths = (64, 128, 192, 256, 384, 512, 768, 1024, 2048, 4096, 8192, 16384, 32768)[:13 if d == 256 else 12]
+        if d == 64:
+            lengths = (512, 1024, 2048, 4096, 8192, 16384)
         for causal in masks:
             grid = [(n, bh) for n in lengths for bh in heads]
-            if d == 128 and not causal:  # one round of narrow tiles and a few more, which the grid passes over
+            if d != 64 and not causal:  # one round of 128-row tiles and a few more, which the grid passes over
                 grid += [(n, 36864 // n) for n in (384, 768, 1536, 3072, 6144, 12288)]
             for n, bh in grid:
                 flops = 4.0 * bh * n * n * d * 2.5 / (2 if causal else 1)
